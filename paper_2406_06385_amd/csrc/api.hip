@@ -83,7 +83,7 @@ struct Dims {
 };
 
 struct Workspace {
-  size_t q = 0, mask = 0, n = 0, xh = 0, sx = 0, dA_part = 0, dB_part = 0, ds_part = 0, dW = 0, total = 0;
+  size_t q = 0, mask = 0, n = 0, xh = 0, sx = 0, nsum = 0, dA_part = 0, dB_part = 0, ds_part = 0, dW = 0, total = 0;
 };
 
 lrqat_status check_layer(const lrqat_layer* L, Dims& d) {
@@ -150,6 +150,7 @@ Workspace layout(const Dims& d, int64_t T, Pass pass) {
     } else {
       w.n = take(size_t(T * d.kpad));
       w.sx = take(size_t(T * 4));
+      w.nsum = take(size_t(T * 4));
     }
   }
   if (pass == kBackward) {
@@ -220,10 +221,11 @@ lrqat_status weight_gemm_forward(const Dims& d, int64_t tokens, const void* X, c
   }
   int8_t* n = reinterpret_cast<int8_t*>(base + w.n);
   float* sx = reinterpret_cast<float*>(base + w.sx);
+  int32_t* nsum = reinterpret_cast<int32_t*>(base + w.nsum);
   if (d.act)
     LRQAT_TRY(hip_status(timed("act_quant", st, [&] {
                            return launch_act_quant(static_cast<const uint16_t*>(X), tokens, d.k, n, d.kpad, nullptr, 0,
-                                                   sx, st);
+                                                   sx, nsum, st);
                          }), "act_quant"));
   GemmArgs p{};
   p.M = tokens; p.N = d.m; p.K = d.k;
@@ -232,7 +234,10 @@ lrqat_status weight_gemm_forward(const Dims& d, int64_t tokens, const void* X, c
   p.b = q; p.ldb = ldq;
   p.s = s; p.z = z; p.gsize = d.g; p.ngroups = d.ngroups;
   p.sx = d.act ? sx : nullptr;
+  p.nsum = d.act ? nsum : nullptr;
   p.out = Y; p.ldo = d.m;
+  if (tokens <= kSmallTokens)
+    return hip_status(timed("gemm_fwd", st, [&] { return launch_fwd_small(d.act, d.g != 0, d.q8w, p, st); }), "gemm_fwd");
   const int opt = (z ? kOptZ : 0) | (d.q8w ? kOptQ8 : 0);
   return hip_status(timed("gemm_fwd", st, [&] { return launch_gemm(kFwd, d.act, d.g != 0, opt, p, st); }), "gemm_fwd");
 }
@@ -368,7 +373,7 @@ lrqat_status backward_impl(const lrqat_layer* layer, int64_t tokens, const void*
   if (d.act)
     LRQAT_TRY(hip_status(timed("act_quant", st, [&] {
                            return launch_act_quant(static_cast<const uint16_t*>(X), tokens, d.k, nullptr, 0, xh,
-                                                   d.kpad, nullptr, st);
+                                                   d.kpad, nullptr, nullptr, st);
                          }), "act_quant"));
   if (dX) {
     GemmArgs p{};
@@ -592,7 +597,8 @@ lrqat_status lrqat_infer_forward(const lrqat_layer* layer, int64_t tokens, const
   di.q8w = 0;  // merged weights are always packed int4
   const uint8_t* q = W_int4;
   int64_t ldq = d.k / 2;
-  if (d.k % 32) {
+  // (the few-token kernel reads rows at any alignment)
+  if (d.k % 32 && !(d.bf16 && tokens <= kSmallTokens)) {
     // rows of k/2 bytes are not 16-byte aligned: copy them into zero-padded rows of kpad/2 bytes
     uint8_t* qp = base + w.q;
     LRQAT_TRY(hip_status(timed("infer_relayout", st, [&] {

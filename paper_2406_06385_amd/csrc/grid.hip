@@ -1213,13 +1213,13 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
 // ============================================================================ activations
 // One block per token row: s_x = max|X_t| / 127, n = clip(round(X_t / s_x), -128, 127).
 // Outputs (each optional): the codes n [T][ldn] (columns k..ldn-1 written as
-// 0), X_hat = s_x n rounded to bfloat16 [T][ldh], and s_x [T].  VEC: k % 8 == 0
+// 0), X_hat = s_x n rounded to bfloat16 [T][ldh], s_x [T] and the sums of the codes nsum [T].  VEC: k % 8 == 0
 // and 16-byte aligned rows, read and written as 16-byte vectors.
 template <bool VEC>
 __global__ __launch_bounds__(256) void k_act_quant(const uint16_t* __restrict__ X, int64_t k,
                                                    int8_t* __restrict__ n, int64_t ldn,
                                                    uint16_t* __restrict__ xh, int64_t ldh,
-                                                   float* __restrict__ sx) {
+                                                   float* __restrict__ sx, int32_t* __restrict__ nsum) {
   const int64_t row = blockIdx.x;
   const uint16_t* x = X + row * k;
   float amax = 0.f;
@@ -1239,6 +1239,7 @@ __global__ __launch_bounds__(256) void k_act_quant(const uint16_t* __restrict__ 
   amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   const float s = amax / 127.f;
   if (threadIdx.x == 0 && sx) sx[row] = s;
+  int total = 0;  // the thread's part of the row's sum of codes
   auto code = [&](float v) { return s > 0.f ? min(max(int(__builtin_rintf(v / s)), -128), 127) : 0; };
   if (VEC) {
     for (int64_t j = 8 * threadIdx.x; j < k; j += 8 * 256) {
@@ -1248,6 +1249,7 @@ __global__ __launch_bounds__(256) void k_act_quant(const uint16_t* __restrict__ 
       for (int q = 0; q < 4; ++q) {
         c[2 * q] = code(bf16_lo(v[q]));
         c[2 * q + 1] = code(bf16_hi(v[q]));
+        total += c[2 * q] + c[2 * q + 1];
       }
       if (n) {
         u32x2 o;
@@ -1270,9 +1272,17 @@ __global__ __launch_bounds__(256) void k_act_quant(const uint16_t* __restrict__ 
     const int64_t end = n ? ldn : k;
     for (int64_t j = threadIdx.x; j < end; j += 256) {
       const int c = j < k ? code(bf16_to_f32(x[j])) : 0;
+      total += c;
       if (n) n[row * ldn + j] = int8_t(c);
       if (xh && j < k) xh[row * ldh + j] = __builtin_bit_cast(uint16_t, (__bf16)(float(c) * s));
     }
+  }
+  if (nsum) {  // uniform
+    for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
+    __shared__ int redi[4];
+    if ((threadIdx.x & 63) == 0) redi[threadIdx.x >> 6] = total;
+    __syncthreads();
+    if (threadIdx.x == 0) nsum[row] = redi[0] + redi[1] + redi[2] + redi[3];
   }
 }
 
@@ -1401,13 +1411,13 @@ hipError_t launch_grid(const GridArgs& a0, hipStream_t st) {
 }
 
 hipError_t launch_act_quant(const uint16_t* X, int64_t T, int64_t k, int8_t* n, int64_t ldn, uint16_t* xh, int64_t ldh,
-                            float* sx, hipStream_t st) {
+                            float* sx, int32_t* nsum, hipStream_t st) {
   if (T == 0) return hipSuccess;
   const bool vec = k % 8 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0 && (!n || ldn % 8 == 0) &&
                    (!xh || (ldh % 8 == 0 && (reinterpret_cast<uintptr_t>(xh) & 15) == 0)) &&
                    (reinterpret_cast<uintptr_t>(n) & 7) == 0;
-  if (vec) k_act_quant<true><<<unsigned(T), 256, 0, st>>>(X, k, n, ldn, xh, ldh, sx);
-  else k_act_quant<false><<<unsigned(T), 256, 0, st>>>(X, k, n, ldn, xh, ldh, sx);
+  if (vec) k_act_quant<true><<<unsigned(T), 256, 0, st>>>(X, k, n, ldn, xh, ldh, sx, nsum);
+  else k_act_quant<false><<<unsigned(T), 256, 0, st>>>(X, k, n, ldn, xh, ldh, sx, nsum);
   return hipGetLastError();
 }
 

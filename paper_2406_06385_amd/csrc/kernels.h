@@ -41,6 +41,7 @@ struct GemmArgs {
   const int32_t* z;       // zero offset, shaped like s (variants with kOptZ)
   int64_t gsize, ngroups;
   const float* sx;        // per-token activation scale [T] (W4A8) or null
+  const int32_t* nsum;    // per-token sum of the activation codes [T] (W4A8 with an int8 MFMA)
   void* out;              // kFwd: Y [T][m]; kDx: dX [T][k]
   int64_t ldo;
   const uint16_t* mask;   // kDw: clip-mask bits, bit (col % 16) of word [row][col / 16]
@@ -70,9 +71,10 @@ hipError_t launch_minmax_scale(const float* W0, int64_t m, int64_t k, int64_t gs
 hipError_t launch_encode(const float* W0, const float* s0, const int32_t* z0, int64_t m, int64_t k, int64_t gsize,
                          int bits, int packed, void* phi0, hipStream_t st);
 hipError_t launch_grid(const GridArgs& a, hipStream_t st);
-// per-token int8 quantisation of bf16 X [T][k]: codes n [T][ldn] and/or X_hat in bf16 [T][ldh] (nullable), s_x [T]
+// per-token int8 quantisation of bf16 X [T][k]: codes n [T][ldn] and/or X_hat in bf16 [T][ldh] (nullable), s_x [T],
+// sums of the codes nsum [T] (nullable)
 hipError_t launch_act_quant(const uint16_t* X, int64_t T, int64_t k, int8_t* n, int64_t ldn, uint16_t* xh, int64_t ldh,
-                            float* sx, hipStream_t st);
+                            float* sx, int32_t* nsum, hipStream_t st);
 // opt: kOpt* flags (forward and dX; the dW GEMM takes its options at run time)
 hipError_t launch_gemm(GemmVariant v, bool act, bool grouped, int opt, const GemmArgs& p, hipStream_t st);
 // per-family launchers, one translation unit each for parallel builds
@@ -84,6 +86,12 @@ hipError_t launch_dx_i4(bool grouped, bool zp, const GemmArgs& p, hipStream_t st
 hipError_t launch_dx_i8(bool grouped, bool zp, const GemmArgs& p, hipStream_t st);       // gemm_dx_q8.hip
 hipError_t launch_dw_pc(const GemmArgs& p, hipStream_t st);                              // gemm_dw.hip
 hipError_t launch_dw_grp(const GemmArgs& p, hipStream_t st);                             // gemm_dw_grp.hip
+// few tokens, weights streamed: gemm_small.hip.  At 128 tokens it is ahead of the
+// general GEMM on every layer measured (4096 x 4096 49 against 84 us, 4096 x 14336
+// 203 against 275, 14336 x 4096 72 against 86); past that its token groups start over
+// and read the weights twice.
+constexpr int64_t kSmallTokens = 128;
+hipError_t launch_fwd_small(bool act, bool grouped, bool q8, const GemmArgs& p, hipStream_t st);
 // rows of w bytes re-laid with a leading dimension of ldd bytes, zero-filled
 hipError_t launch_repack_rows(const uint8_t* src, int64_t m, int64_t w, uint8_t* dst, int64_t ldd, hipStream_t st);
 // ds[row][grp] = (accumulate ? ds : 0) + sum of the 32-column chunk partials of the group
