@@ -74,7 +74,7 @@ inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 inline bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
 struct Dims {
-  int64_t m, k, r, g, ngroups, kpad, mpad;
+  int64_t m, k, r, g, ngroups, kpad;
   int bits, packed, act, bf16;
   int q8w;  // the integer grid is kept as int8 (fixed-point Phi0 with b = 5..7)
   float c;
@@ -84,6 +84,7 @@ struct Dims {
 
 struct Workspace {
   size_t q = 0, mask = 0, n = 0, xh = 0, sx = 0, nsum = 0, dA_part = 0, dB_part = 0, ds_part = 0, dW = 0, total = 0;
+  GemmPlan dw;
 };
 
 lrqat_status check_layer(const lrqat_layer* L, Dims& d) {
@@ -119,8 +120,7 @@ lrqat_status check_layer(const lrqat_layer* L, Dims& d) {
   d.r = L->rank;
   d.g = L->group_size;
   d.ngroups = d.g ? d.k / d.g : 1;
-  d.kpad = round_up(d.k, GEMM_BN);
-  d.mpad = round_up(d.m, GEMM_BM);
+  d.kpad = round_up(d.k, kColPad);
   d.bits = L->bits;
   d.packed = L->phi_format == LRQAT_PHI_INT_PACKED2;
   d.q8w = !d.packed && d.bits > 4;
@@ -133,8 +133,10 @@ lrqat_status check_layer(const lrqat_layer* L, Dims& d) {
 
 enum Pass { kForward, kBackward, kInfer };
 
-Workspace layout(const Dims& d, int64_t T, Pass pass) {
+// The layout for a plan of the dW GEMM (its partial sums are in the workspace).
+Workspace layout_plan(const Dims& d, int64_t T, Pass pass, const GemmPlan& dw) {
   Workspace w;
+  w.dw = dw;
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t at = off;
@@ -154,17 +156,30 @@ Workspace layout(const Dims& d, int64_t T, Pass pass) {
     }
   }
   if (pass == kBackward) {
-    w.ds_part = take(size_t(d.m * (d.kpad / 32) * 4));
     if (d.bf16) {
-      const int64_t ntn = (d.k + GEMM_BN - 1) / GEMM_BN, ntm = (d.m + GEMM_BM - 1) / GEMM_BM;
-      w.dA_part = take(size_t(ntn * d.m * d.r * 4));
-      w.dB_part = take(size_t(ntm * d.r * d.k * 4));
+      w.ds_part = take(size_t(dw.split * d.m * (d.kpad / 32) * 4));
+      const int64_t ntn = (d.k + dw.tn - 1) / dw.tn, ntm = (d.m + dw.tm - 1) / dw.tm;
+      w.dA_part = take(size_t(dw.split * ntn * d.m * d.r * 4));
+      w.dB_part = take(size_t(dw.split * ntm * d.r * d.k * 4));
     } else {
       w.dW = take(size_t(d.m * d.k * 4));
     }
   }
   w.total = off;
   return w;
+}
+
+constexpr size_t kStaticScratchBytes = size_t(64) << 20;  // the scratch array of lrqat_backward_static
+
+Workspace layout(const Dims& d, int64_t T, Pass pass) {
+  if (pass != kBackward || !d.bf16 || T == 0) return layout_plan(d, T, pass, {});
+  const GemmPlan dw = gemm_plan(kDw, false, d.g != 0, true, d.m, d.k, T);
+  const Workspace w = layout_plan(d, T, pass, dw);
+  if (dw.split == 1 || w.total <= kStaticScratchBytes) return w;
+  // A layer that fits the scratch array of lrqat_backward_static only with one set of partial sums takes
+  // one, in both entry points (so that they give the same bits).
+  const Workspace w1 = layout_plan(d, T, pass, {});
+  return w1.total <= kStaticScratchBytes ? w1 : w;
 }
 
 GridArgs grid_args(const Dims& d, const void* phi0, const float* A, const float* B, uint8_t* q, uint16_t* mask) {
@@ -236,6 +251,7 @@ lrqat_status weight_gemm_forward(const Dims& d, int64_t tokens, const void* X, c
   p.sx = d.act ? sx : nullptr;
   p.nsum = d.act ? nsum : nullptr;
   p.out = Y; p.ldo = d.m;
+  p.plan = gemm_plan(kFwd, d.act, d.g != 0, gemm_al16(kFwd, d.act, p.K, p.lda, p.ldb), p.M, p.N, p.K);
   if (tokens <= kSmallTokens)
     return hip_status(timed("gemm_fwd", st, [&] { return launch_fwd_small(d.act, d.g != 0, d.q8w, p, st); }), "gemm_fwd");
   const int opt = (z ? kOptZ : 0) | (d.q8w ? kOptQ8 : 0);
@@ -382,6 +398,7 @@ lrqat_status backward_impl(const lrqat_layer* layer, int64_t tokens, const void*
     p.b = q; p.ldb = ga.ldq;
     p.s = s; p.z = z; p.gsize = d.g; p.ngroups = d.ngroups;
     p.out = dX; p.ldo = d.k;
+    p.plan = gemm_plan(kDx, false, d.g != 0, gemm_al16(kDx, false, p.K, p.lda, p.ldb), p.M, p.N, p.K);
     const int opt = (z ? kOptZ : 0) | (d.q8w ? kOptQ8 : 0);
     LRQAT_TRY(hip_status(timed("gemm_dx", st, [&] { return launch_gemm(kDx, false, d.g != 0, opt, p, st); }),
                          "gemm_dx"));
@@ -398,12 +415,13 @@ lrqat_status backward_impl(const lrqat_layer* layer, int64_t tokens, const void*
   p.mask = mask; p.ldm = ga.ldm;
   p.Am = A; p.Bm = B; p.r = int(d.r);
   p.dA_part = dA_part; p.dB_part = dB_part;
+  p.plan = w.dw;
   if (ds) {
     p.qd = q; p.ldqd = ga.ldq; p.qd8 = d.q8w;
     p.ds_part = ds_part; p.ldds = d.kpad / 32;
   }
   LRQAT_TRY(hip_status(timed("gemm_dw", st, [&] { return launch_gemm(kDw, false, d.g != 0, 0, p, st); }), "gemm_dw"));
-  const int64_t ntn = (d.k + GEMM_BN - 1) / GEMM_BN, ntm = (d.m + GEMM_BM - 1) / GEMM_BM;
+  const int64_t ntn = w.dw.split * ((d.k + w.dw.tn - 1) / w.dw.tn), ntm = w.dw.split * ((d.m + w.dw.tm - 1) / w.dw.tm);
   Reduce2Args ra{};
   ra.part[0] = dA_part; ra.nparts[0] = ntn; ra.n[0] = d.m * d.r; ra.out[0] = dA;
   ra.part[1] = dB_part; ra.nparts[1] = ntm; ra.n[1] = d.r * d.k; ra.out[1] = dB;
@@ -414,7 +432,7 @@ lrqat_status backward_impl(const lrqat_layer* layer, int64_t tokens, const void*
   if (ds) {
     const int64_t nchunks = (d.k + 31) / 32, cpg = d.g ? d.g / 32 : nchunks;
     LRQAT_TRY(hip_status(timed("reduce_ds", st, [&] {
-                           return launch_reduce_ds(ds_part, d.m, d.kpad / 32, nchunks, cpg, d.ngroups, ds, accumulate, st);
+                           return launch_reduce_ds(ds_part, d.m, d.kpad / 32, nchunks, cpg, d.ngroups, w.dw.split, ds, accumulate, st);
                          }), "reduce_ds"));
   }
   return LRQAT_OK;
@@ -424,7 +442,6 @@ lrqat_status backward_impl(const lrqat_layer* layer, int64_t tokens, const void*
 // One array per GPU (each device holds its own copy of a __device__ variable),
 // kept until the process ends.  Host code never passes `scratch` itself to a
 // kernel: its device address is looked up once per device.
-constexpr size_t kStaticScratchBytes = size_t(64) << 20;
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};

@@ -57,6 +57,14 @@ __device__ __forceinline__ f32x16 mfma32(const u32x4& a, const u32x4& b, const f
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
+// D(32x32, i32) += A(32x32, i8) * B(32x32, i8): as above with 16 K-values per lane; the int32
+// accumulators are carried as bits of f32x16.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ f32x16 mfma32_i8(const u32x4& a, const u32x4& b, const f32x16& c) {
+  return __builtin_bit_cast(f32x16, __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b),
+                                                                          __builtin_bit_cast(i32x16, c), 0, 0, 0));
+}
 __device__ __forceinline__ int acc_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
 // ---------------------------------------------------------------- the grid decision

@@ -1,6 +1,8 @@
 // Dispatch of the bf16 MFMA GEMM variants (one translation unit per variant
 // family, see gemm_impl.h) and the deterministic reduction of the rank-r
 // partial products.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace lrqat {
@@ -57,10 +59,57 @@ hipError_t launch_reduce2(const Reduce2Args& ra, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Tiles: the time of a launch is its rounds over the chip (256 CUs; two 128 x 128 blocks share one) times
+// the time of a round, and a 256 x 256 tile has the best rate but leaves CUs idle when an output has few
+// of them.  The weights below are rounds of each tile against a round of 256 x 256 tiles, measured on
+// outputs that fill the chip (4096 x 4096, T = 8192: forward 226 us with 256 x 256 tiles, 251 / 286 / 279 with
+// 256 x 128, 128 x 256, 128 x 128; dX 246, 289 / 312 / 347) or at most once.  What the choice gives: forward of
+// 640 tokens through 11008 x 4096 (129 tiles of 256 x 256) 98 -> 70 us, of 4096 tokens through 1024 x 4096 94 ->
+// 49; dX of 2048 tokens through 14336 x 4096 (128 tiles) 339 -> 254.
+//
+// dW: its epilogue's partial sums grow with the number of tiles, so tiles stay 256 x 256 and an output with
+// fewer than one per CU splits the tokens instead, as far as every block keeps six K-tiles (its epilogue
+// costs about ten): 1024 x 4096, T = 4096 144 -> 62 us in four splits.
+GemmPlan gemm_plan(GemmVariant v, bool act, bool grouped, bool al16, int64_t M, int64_t N, int64_t K) {
+  GemmPlan g;
+  auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+  if (v == kDw) {
+    const int64_t nk = (K + 63) / 64, most = std::min<int64_t>(256 / std::max<int64_t>(tiles(256, 256), 1), nk / 6);
+    if (most > 1) {
+      g.kts = (nk + most - 1) / most;
+      g.split = int((nk + g.kts - 1) / g.kts);
+    }
+    return g;
+  }
+  if (!al16) {  // rows off 16 bytes: the small tile, whose second block per CU hides the loads that cross lines
+    g.tm = g.tn = 128;
+    return g;
+  }
+  struct Cost { double t42, t24, t22, t22_one; };  // a round of 256 x 128, 128 x 256, 128 x 128 (two and one per CU)
+  constexpr double never = 1e30;  // the other tiles are ahead wherever it could be taken
+  const Cost c = v == kFwd ? (act ? Cost{never, never, 0.54, 0.46} : Cost{0.57, never, 0.63, 0.44})
+                           : (grouped ? Cost{0.78, 0.74, 0.88, 0.55} : Cost{0.59, 0.63, 0.70, 0.45});
+  auto rounds = [](int64_t n, int64_t slots) { return double((n + slots - 1) / slots); };
+  double best = rounds(tiles(256, 256), 256);
+  auto offer = [&](int tm, int tn, double cost) {
+    if (cost < best) {
+      best = cost;
+      g.tm = tm;
+      g.tn = tn;
+    }
+  };
+  offer(256, 128, rounds(tiles(256, 128), 256) * c.t42);
+  offer(128, 256, rounds(tiles(128, 256), 256) * c.t24);
+  const int64_t n22 = tiles(128, 128);
+  offer(128, 128, n22 <= 256 ? c.t22_one : rounds(n22, 512) * c.t22);
+  return g;
+}
+
 hipError_t launch_gemm(GemmVariant v, bool act, bool grouped, int opt, const GemmArgs& p, hipStream_t st) {
   const bool zp = (opt & kOptZ) != 0, i8 = (opt & kOptQ8) != 0;
   switch (v) {
     case kFwd:
+      if (fwd_int8(act, grouped, p.K)) return launch_fwd_int8(i8, zp, p, st);
       if (act) return i8 ? launch_fwd_act_i8(grouped, zp, p, st) : launch_fwd_act_i4(grouped, zp, p, st);
       return i8 ? launch_fwd_i8(grouped, zp, p, st) : launch_fwd_i4(grouped, zp, p, st);
     case kDx:
@@ -72,32 +121,37 @@ hipError_t launch_gemm(GemmVariant v, bool act, bool grouped, int opt, const Gem
   return hipErrorInvalidValue;
 }
 
-// ds[row][grp] = (accumulate ? ds : 0) + the partials of the group's 32-column chunks, summed in
-// chunk order (deterministic).  One thread per (row, group).
+// ds[row][grp] = (accumulate ? ds : 0) + the partials of the group's 32-column chunks over all splits.
+// 2^lg consecutive lanes share a (row, group): each takes every 2^lg-th chunk (coalesced), and their sums
+// meet in a fixed tree, so the result is deterministic.  (One thread per row, whose loads are a row apart,
+// took 47 us for 4096 rows of 344 chunks.)
 __global__ __launch_bounds__(256) void k_reduce_ds(const float* __restrict__ part, int64_t m, int64_t ldpart,
-                                                   int64_t nchunks, int64_t cpg, int64_t ngroups,
+                                                   int64_t nchunks, int64_t cpg, int64_t ngroups, int nsplit, int lg,
                                                    float* __restrict__ ds, int accumulate) {
-  const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (idx >= m * ngroups) return;
-  const int64_t row = idx / ngroups, grp = idx % ngroups;
-  const int64_t c0 = grp * cpg, c1 = min(nchunks, c0 + cpg);
-  const float* src = part + row * ldpart;
-  float s0 = 0.f, s1 = 0.f;
-  int64_t c = c0;
-  for (; c + 2 <= c1; c += 2) {
-    s0 += src[c];
-    s1 += src[c + 1];
+  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x, idx = t >> lg;
+  const bool in = idx < m * ngroups;
+  const int l = int(t & ((1 << lg) - 1));
+  float s = 0.f;
+  if (in) {
+    const int64_t row = idx / ngroups, grp = idx % ngroups;
+    const int64_t c0 = grp * cpg, c1 = min(nchunks, c0 + cpg);
+    for (int q = 0; q < nsplit; ++q) {
+      const float* src = part + (q * m + row) * ldpart;
+      for (int64_t c = c0 + l; c < c1; c += int64_t(1) << lg) s += src[c];
+    }
   }
-  if (c < c1) s0 += src[c];
-  ds[idx] = (accumulate ? ds[idx] : 0.f) + (s0 + s1);
+  for (int off = (1 << lg) >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  if (in && l == 0) ds[idx] = (accumulate ? ds[idx] : 0.f) + s;
 }
 
 hipError_t launch_reduce_ds(const float* part, int64_t m, int64_t ldpart, int64_t nchunks, int64_t chunks_per_group,
-                            int64_t ngroups, float* ds, int accumulate, hipStream_t st) {
+                            int64_t ngroups, int nsplit, float* ds, int accumulate, hipStream_t st) {
   const int64_t n = m * ngroups;
   if (n == 0) return hipSuccess;
-  k_reduce_ds<<<unsigned((n + 255) / 256), 256, 0, st>>>(part, m, ldpart, nchunks, chunks_per_group, ngroups, ds,
-                                                         accumulate);
+  int lg = 0;  // lanes per sum: up to a wave, no more than its chunks
+  while (lg < 6 && (int64_t(2) << lg) <= chunks_per_group) ++lg;
+  k_reduce_ds<<<unsigned(((n << lg) + 255) / 256), 256, 0, st>>>(part, m, ldpart, nchunks, chunks_per_group, ngroups, nsplit,
+                                                                 lg, ds, accumulate);
   return hipGetLastError();
 }
 

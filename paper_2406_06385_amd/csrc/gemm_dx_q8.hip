@@ -3,6 +3,6 @@
 
 namespace lrqat {
 
-hipError_t launch_dx_i8(bool grouped, bool zp, const GemmArgs& p, hipStream_t st) { return launch_zg<kDx, false, kOptQ8>(grouped, zp, p, st); }
+hipError_t launch_dx_i8(bool grouped, bool zp, const GemmArgs& p, hipStream_t st) { return launch_zg<kDx, kActNone, kOptQ8>(grouped, zp, p, st); }
 
 }  // namespace lrqat

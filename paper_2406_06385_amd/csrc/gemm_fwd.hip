@@ -3,6 +3,6 @@
 
 namespace lrqat {
 
-hipError_t launch_fwd_i4(bool grouped, bool zp, const GemmArgs& p, hipStream_t st) { return launch_zg<kFwd, false, 0>(grouped, zp, p, st); }
+hipError_t launch_fwd_i4(bool grouped, bool zp, const GemmArgs& p, hipStream_t st) { return launch_zg<kFwd, kActNone, 0>(grouped, zp, p, st); }
 
 }  // namespace lrqat

@@ -3,6 +3,6 @@
 
 namespace lrqat {
 
-hipError_t launch_fwd_i8(bool grouped, bool zp, const GemmArgs& p, hipStream_t st) { return launch_zg<kFwd, false, kOptQ8>(grouped, zp, p, st); }
+hipError_t launch_fwd_i8(bool grouped, bool zp, const GemmArgs& p, hipStream_t st) { return launch_zg<kFwd, kActNone, kOptQ8>(grouped, zp, p, st); }
 
 }  // namespace lrqat

@@ -26,8 +26,6 @@ namespace lrqat {
 
 namespace {
 
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
 enum SmallMode { kSmallBf16 = 0, kSmallI8 = 1, kSmallI8Wide = 2 };  // X in bf16; codes on the int8 MFMA; codes widened to bf16
 
 __device__ __forceinline__ f32x4 mfma16_bf16(const u32x4& p, const u32x4& q, const f32x4& c) {
@@ -37,10 +35,6 @@ __device__ __forceinline__ f32x4 mfma16_i8(const u32x4& p, const u32x4& q, const
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, p), __builtin_bit_cast(i32x4, q),
                                                                         __builtin_bit_cast(i32x4, c), 0, 0, 0));
 }
-
-// Resource over `bytes` bytes, rounded up to whole dwords: the range check of
-// a multi-dword load works per dword, so a last half dword would read as zero.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc4(const void* base, int64_t bytes) { return rsrc(base, (bytes + 3) & ~int64_t(3)); }
 
 // 16 bytes at any byte offset: dword-aligned loads, shifted into place.
 __device__ __forceinline__ u32x4 ld128_any(__amdgpu_buffer_rsrc_t r, uint32_t off) {
@@ -253,8 +247,7 @@ hipError_t launch_fwd_small(bool act, bool grouped, bool q8, const GemmArgs& p, 
     if (grouped) return q8 ? launch_mode<kSmallBf16, true, true>(p, st) : launch_mode<kSmallBf16, true, false>(p, st);
     return q8 ? launch_mode<kSmallBf16, false, true>(p, st) : launch_mode<kSmallBf16, false, false>(p, st);
   }
-  // int32 sums of products up to 2^14 (16 q n) cannot wrap up to K = 2^16
-  if (grouped || p.K > (int64_t(1) << 16)) {
+  if (!fwd_int8(act, grouped, p.K)) {
     if (grouped) return q8 ? launch_mode<kSmallI8Wide, true, true>(p, st) : launch_mode<kSmallI8Wide, true, false>(p, st);
     return q8 ? launch_mode<kSmallI8Wide, false, true>(p, st) : launch_mode<kSmallI8Wide, false, false>(p, st);
   }

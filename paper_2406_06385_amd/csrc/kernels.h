@@ -31,6 +31,14 @@ struct GridArgs {
 // sources and epilogue chosen by the kernel variant.
 enum GemmVariant { kFwd = 0, kDx = 1, kDw = 2 };
 
+// Work split of a GEMM: block tiles of tm x tn outputs (256 or 128 each); for dW `split` blocks per tile,
+// which take kts K-tiles of 64 tokens each.
+struct GemmPlan {
+  int tm = 256, tn = 256;
+  int split = 1;
+  int64_t kts = 0;
+};
+
 struct GemmArgs {
   int64_t M, N, K;
   const void* a;          // kFwd: X bf16 [T][k] or n int8 [T][lda]; kDx: dY [T][m]; kDw: dY [T][m]
@@ -49,14 +57,19 @@ struct GemmArgs {
   const float* Am;        // kDw: A [m][r]
   const float* Bm;        // kDw: B [r][k]
   int r;
-  float* dA_part;         // kDw: [ceil(N/256)][M][r]
-  float* dB_part;         // kDw: [ceil(M/256)][r][N]
+  float* dA_part;         // kDw: [split][column tiles][M][r]
+  float* dB_part;         // kDw: [split][row tiles][r][N]
   const uint8_t* qd;      // kDw with kOptDs: q [M][ldqd] (packed int4, or int8 with kOptQ8)
   int64_t ldqd;
-  float* ds_part;         // kDw, nullable: [M][ldds], sums over 32-column chunks of dW (q - z)
+  float* ds_part;         // kDw, nullable: [split][M][ldds], sums over 32-column chunks of dW (q - z)
   int64_t ldds;
   int qd8;                // kDw with ds_part: qd is int8
+  GemmPlan plan;
 };
+
+// Activation operand of the forward: bfloat16 X, int8 codes widened to bfloat16 (group-wise scales), or int8
+// codes on the int8 MFMA.
+enum : int { kActNone = 0, kActWide = 1, kActI8 = 2 };
 
 // Variant options of the forward and dX GEMMs (bit flags).
 enum : int {
@@ -64,8 +77,18 @@ enum : int {
   kOptQ8 = 2   // the integer grid q is int8 (grids of 5..7 bits) instead of packed int4
 };
 
-constexpr int GEMM_BM = 256, GEMM_BN = 256, GEMM_BK = 64;
+constexpr int kColPad = 256;  // q, mask and code rows are padded to a multiple of this
 
+// int8 tokens run on the int8 MFMA with one scale per output channel, and where int32 sums of products
+// up to 2^14 (16 q n) cannot wrap
+inline bool fwd_int8(bool act, bool grouped, int64_t K) { return act && !grouped && K <= (int64_t(1) << 16); }
+// plan of a GEMM from its sizes; al16: its bfloat16 rows start on 16 bytes (and a K-contiguous one has no
+// partial K-tile)
+GemmPlan gemm_plan(GemmVariant v, bool act, bool grouped, bool al16, int64_t M, int64_t N, int64_t K);
+inline bool gemm_al16(GemmVariant v, bool act, int64_t K, int64_t lda, int64_t ldb) {
+  if (v == kDw) return lda % 8 == 0 && ldb % 8 == 0;
+  return act || (lda % 8 == 0 && K % 64 == 0);
+}
 hipError_t launch_minmax_scale(const float* W0, int64_t m, int64_t k, int64_t gsize, int bits, float* s0, int32_t* z0,
                                hipStream_t st);
 hipError_t launch_encode(const float* W0, const float* s0, const int32_t* z0, int64_t m, int64_t k, int64_t gsize,
@@ -80,6 +103,7 @@ hipError_t launch_gemm(GemmVariant v, bool act, bool grouped, int opt, const Gem
 // per-family launchers, one translation unit each for parallel builds
 hipError_t launch_fwd_i4(bool grouped, bool zp, const GemmArgs& p, hipStream_t st);      // gemm_fwd.hip
 hipError_t launch_fwd_i8(bool grouped, bool zp, const GemmArgs& p, hipStream_t st);      // gemm_fwd_q8.hip
+hipError_t launch_fwd_int8(bool q8, bool zp, const GemmArgs& p, hipStream_t st);        // gemm_fwd_int8.hip
 hipError_t launch_fwd_act_i4(bool grouped, bool zp, const GemmArgs& p, hipStream_t st);  // gemm_fwd_act.hip
 hipError_t launch_fwd_act_i8(bool grouped, bool zp, const GemmArgs& p, hipStream_t st);  // gemm_fwd_act_q8.hip
 hipError_t launch_dx_i4(bool grouped, bool zp, const GemmArgs& p, hipStream_t st);       // gemm_dx.hip
@@ -96,7 +120,7 @@ hipError_t launch_fwd_small(bool act, bool grouped, bool q8, const GemmArgs& p, 
 hipError_t launch_repack_rows(const uint8_t* src, int64_t m, int64_t w, uint8_t* dst, int64_t ldd, hipStream_t st);
 // ds[row][grp] = (accumulate ? ds : 0) + sum of the 32-column chunk partials of the group
 hipError_t launch_reduce_ds(const float* part, int64_t m, int64_t ldpart, int64_t nchunks, int64_t chunks_per_group,
-                            int64_t ngroups, float* ds, int accumulate, hipStream_t st);
+                            int64_t ngroups, int nsplit, float* ds, int accumulate, hipStream_t st);
 hipError_t launch_reduce(const float* part, int64_t nparts, int64_t n, float* out, float c, int accumulate,
                          hipStream_t st);
 struct Reduce2Args {        // side 0: dA, side 1: dB
