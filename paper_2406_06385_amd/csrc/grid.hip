@@ -177,7 +177,8 @@ __device__ __forceinline__ void load_phi(PhiRegs& P, const GridArgs& a, int64_t 
   const int lane = threadIdx.x & 63;
   const int nb = PACKED ? 8 : 16;
   const int64_t row0 = rowblk * 16, cb0 = PACKED ? col0 / 2 : col0;
-  const auto r = grid_rsrc(a.phi0 + row0 * a.ld_phi + cb0, (a.m - row0) * a.ld_phi - cb0);
+  // (a base on 16 bytes: row0 is a multiple of 16; the size rounded up to whole dwords, the unit of the range check)
+  const auto r = grid_rsrc(a.phi0 + row0 * a.ld_phi + cb0, ((a.m - row0) * a.ld_phi - cb0 + 3) & ~int64_t(3));
   const uint32_t off = uint32_t((lane & 15) * a.ld_phi + nb * (lane >> 4));
   if (vec) {
     if constexpr (PACKED) {
@@ -191,10 +192,20 @@ __device__ __forceinline__ void load_phi(PhiRegs& P, const GridArgs& a, int64_t 
       for (int q = 0; q < 4; ++q) P.w[q] = v[q];
     }
   } else {
+    // rows that start anywhere: whole dwords, shifted into place
+    const uint32_t o = off & ~3u;
+    if constexpr (PACKED) {
+      const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, int(o), 0, 0));
+      const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(r, int(o + 8), 0, 0);
+      P.w[0] = __builtin_amdgcn_alignbyte(v[1], v[0], off & 3u);
+      P.w[1] = __builtin_amdgcn_alignbyte(x, v[1], off & 3u);
+      P.w[2] = P.w[3] = 0u;
+    } else {
+      const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, int(o), 0, 0));
+      const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(r, int(o + 16), 0, 0);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) P.w[q] = 0u;
-    for (int b = 0; b < nb; ++b)
-      P.w[b >> 2] |= uint32_t(__builtin_amdgcn_raw_buffer_load_b8(r, int(off + b), 0, 0)) << (8 * (b & 3));
+      for (int q = 0; q < 4; ++q) P.w[q] = __builtin_amdgcn_alignbyte(q < 3 ? v[(q + 1) & 3] : x, v[q], off & 3u);
+    }
   }
 }
 
@@ -203,15 +214,6 @@ template <bool PACKED>
 __device__ __forceinline__ int phi_code(const PhiRegs& P, int idx) {
   if constexpr (PACKED) return int(P.w[idx >> 3] << (28 - 4 * (idx & 7))) >> 28;
   else return int(P.w[idx >> 2] << (24 - 8 * (idx & 3))) >> 24;
-}
-
-// The same with a run-time index (the rare float64 path).
-template <bool PACKED>
-__device__ __forceinline__ int phi_code_dyn(const PhiRegs& P, int idx) {
-  const int wi = PACKED ? idx >> 3 : idx >> 2;
-  const uint32_t w = wi == 0 ? P.w[0] : wi == 1 ? P.w[1] : wi == 2 ? P.w[2] : P.w[3];
-  if constexpr (PACKED) return int(w << (28 - 4 * (idx & 7))) >> 28;
-  else return int(w << (24 - 8 * (idx & 3))) >> 24;
 }
 
 // A operand of one K-step: A[row][32 ks + 8 (l / 16) .. +7] of the lane's
@@ -268,21 +270,6 @@ __device__ __forceinline__ uint32_t pack_nibble_bytes(uint32_t q0, uint32_t q1) 
   return __builtin_amdgcn_perm(q1 | (q1 >> 4), q0 | (q0 >> 4), 0x06040200u);
 }
 
-// Rounding decision, clip, packing and mask of one 16 x 64 wave tile, by the
-// cheapest of the paths that is exact for the whole wave (INT-b Phi0 whose
-// |delta| bound is below 1/2 on the whole tile has been copied already):
-//  * delta identically zero on the strip (B = 0, the adapters' initial
-//    state): round-half-even of Phi0, decided in integers;
-//  * byte-parallel (swar_grid_q8): every |delta| is below the distance of the
-//    non-tie codes to their rounding points and, at ties, above the error bound
-//    tau, so only a tie depends on delta, through its sign; INT4 Phi0 is then q
-//    itself.  Codes that would round off the grid send the wave on;
-//  * per element: with Phi0 = n + cf 2^-f (n = floor, cf the f fraction bits),
-//    u = n + 1/2 + w and w = (cf 2^-f - 1/2) + delta, one fused multiply-add of
-//    exact terms; for w strictly between the integers j - 1 and j the nearest
-//    integer to u is n + j = n + ceil(w).  That is certain unless w lies within
-//    the error bound of an integer; a wave with such an element redoes its tile
-//    with exact margins and float64 deltas (rare).
 // The lane's results for its 16 columns: q as 16 nibbles (w0, w1) or 16 bytes
 // (qb, Q8OUT), and the clip-mask bits.
 struct GridOut {
@@ -291,196 +278,199 @@ struct GridOut {
   uint32_t mb;
 };
 
+// Columns of q at or past k are written as 0.
+__device__ __forceinline__ void grid_clear(const GridArgs& a, GridOut& o, int64_t c16, bool q8out) {
+  const int kin = int(max<int64_t>(0, min<int64_t>(16, a.k - c16)));  // the lane's columns inside k
+  if (kin == 16) return;
+  if (q8out) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int nb = kin - 4 * g;  // bytes of word g inside k
+      o.qb[g] &= nb >= 4 ? 0xFFFFFFFFu : nb <= 0 ? 0u : (1u << (8 * nb)) - 1u;
+    }
+  } else {
+    const uint64_t keep = (uint64_t(1) << (4 * kin)) - 1;  // kin <= 15
+    o.w0 &= uint32_t(keep);
+    o.w1 &= uint32_t(keep >> 32);
+  }
+}
+
+// Rounding decision, clip, packing and mask of one 16 x 64 wave tile (INT-b Phi0 whose |delta| bound is
+// below 1/2 on the whole tile has been copied already).  Returns whether one of
+// the lane's elements lies within the error bound tau of a rounding point: its result is tentative, and the
+// lane's piece is to be queued for grid_drain.
+//  * Q8, |delta| < 1/2: with Phi0 = n + cf 2^-f (n = floor, cf the f fraction bits), u = n + 1/2 + w,
+//    w = (cf 2^-f - 1/2) + delta (one fused multiply-add of exact terms, which keeps the sign of w at any
+//    size of delta), the nearest integer is n + [w > 0], formed byte-parallel;
+//  * else u = Phi0 + delta is rounded in float32 by adding 1.5 2^23: the nearest integer v is then the low
+//    byte (two's complement) of the sum's bits.  Where delta is identically zero (tau < 0: a zero A row;
+//    zero_delta: zero B columns, the adapters' initial state) this is round-half-even of Phi0 itself.
+// edge (uniform): the tile has columns past k.
 template <bool PACKED, bool MASK, bool B4, bool Q8OUT>
-__device__ __forceinline__ void grid_decide(const GridArgs& a, const PhiRegs& P, const f32x4 (&acc)[4], float tau,
-                                            bool zero_delta, int64_t row, int64_t c16, bool small_delta,
-                                            GridOut& o) {
+__device__ __forceinline__ bool grid_decide(const GridArgs& a, const PhiRegs& P, const f32x4 (&acc)[4], float tau, bool zero_delta,
+                                                int64_t row, int64_t c16, bool edge, GridOut& o) {
   const int bits = B4 ? 4 : a.bits;  // B4: the common 4-bit grid, constant for the compiler
   const int lo = -(1 << (bits - 1)), hi = (1 << (bits - 1)) - 1;
   const int f = PACKED ? 0 : 8 - bits;
-  const bool row_ok = row < a.m;
-  const int kin = int(max<int64_t>(0, min<int64_t>(16, a.k - c16)));  // the lane's columns inside k
-  auto n_of = [&](int idx) { return PACKED ? phi_code<true>(P, idx) : phi_code<false>(P, idx) >> f; };
-
-  int ut[16];
-  uint32_t w0 = 0, w1 = 0;    // 16 nibbles (q as int4)
-  uint32_t qb[4] = {0, 0, 0, 0};  // 16 bytes (q as int8, Q8OUT)
-  uint32_t mb = 0;            // clip-mask bits of the lane's 16 columns
-  bool done = false;  // q words (and an all-ones mask) already formed by the byte-parallel path
-  if constexpr (PACKED) {
-    if (small_delta) {  // the wave tile's |delta| is provably below 1/2: q is Phi0
-      w0 = P.w[0];
-      w1 = P.w[1];
-      mb = 0xFFFFu;
-      done = true;
-    }
-  }
-  if (!done && !zero_delta) {
-    // the regime of the byte-parallel path: every |delta| below the distance of the non-tie
-    // codes to their rounding points and above the error bound (so its sign is certain)
-    const float tz = fmaxf(tau, 0.f);
-    float amx = 0.f, amn = __builtin_inff();
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        amx = fmaxf(amx, fabsf(acc[cb][v]));
-        amn = fminf(amn, fabsf(acc[cb][v]));
-      }
-    const float ac = fabsf(a.c);
-    const float lim = (PACKED ? 0.5f : __builtin_bit_cast(float, uint32_t(127 - f) << 23)) - tz - 0x1p-22f;
-    // INT4 codes have no ties: inside the regime q does not depend on delta at all
-    const bool fast = amx * ac < lim && (PACKED || amn * ac > tz) && a.c != 0.f && (!PACKED || bits == 4);
-    bool regime = amx * ac < lim && a.c != 0.f && (!PACKED || bits == 4);
-    if constexpr (!PACKED) {
-      // A wave whose smallest |delta| is within the bound may still be decidable: only ties
-      // (cf = 2^(f-1)) depend on delta, so check ties against the bound element by element.
-      if (__builtin_amdgcn_ballot_w64(!fast) && !__builtin_amdgcn_ballot_w64(!regime)) {
-        const uint32_t ones = 0x01010101u;
-        // covers the rounding of c * acc; never 0, so that a tie with delta exactly 0 is caught
-        const float tzu = fmaxf(tz * (1.f + 0x1p-20f), 0x1p-100f);
-        uint32_t bad = 0;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          f32x4 d;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) d[v] = __builtin_fmaf(fabsf(acc[g][v]), ac, -tzu);  // < 0: within the bound
-          const uint32_t y = (P.w[g] & (ones * ((1u << f) - 1))) ^ (ones << (f - 1));  // 0 in tie bytes
-          const uint32_t tie = ~((y + 0x7F7F7F7Fu) | y) & 0x80808080u;
-          bad |= sign_bytes(d) & tie;
-        }
-        regime = bad == 0;
-      } else {
-        regime = fast;
-      }
-    }
-    if (!__builtin_amdgcn_ballot_w64(!(PACKED ? fast : regime))) {
-      if constexpr (PACKED) {
-        // |delta| < 1/2: q is Phi0 itself (INT4 codes are always on the grid)
-        w0 = P.w[0];
-        w1 = P.w[1];
-        done = true;
-      } else {
-        uint32_t q[4], clip = 0;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const uint32_t sb = sign_bytes(acc[g]);
-          const uint32_t incb = ((a.c > 0.f ? ~sb : sb) >> 7) & 0x01010101u;
-          q[g] = swar_grid_q8(P.w[g], incb, f, bits, clip);
-        }
-        if (!__builtin_amdgcn_ballot_w64(clip != 0)) {
-          if constexpr (Q8OUT) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) qb[g] = q[g];
-          } else {
-            w0 = pack_nibble_bytes(q[0], q[1]);
-            w1 = pack_nibble_bytes(q[2], q[3]);
-          }
-          done = true;
-        }
-      }
-      if (done) mb = 0xFFFFu;  // inside the regime every rounded value is on the grid
-    }
-  }
-  if (done) {
-  } else if (zero_delta) {
-    // round-half-even of Phi0 = n + cf 2^-f
-    const int half = f ? 1 << (f - 1) : 0;
-#pragma unroll
-    for (int idx = 0; idx < 16; ++idx) {
-      const int code = phi_code<PACKED>(P, idx), n = code >> f, cf = code & ((1 << f) - 1);
-      ut[idx] = f ? n + int(cf > half || (cf == half && (n & 1))) : code;
-    }
-  } else {
-    const float tz = fmaxf(tau, 0.f);
-    const float sf = __builtin_bit_cast(float, uint32_t(127 - f) << 23);  // 2^-f
-    uint64_t flag = 0;
-    // fraction bits of the four codes of each word, as unsigned bytes (Q8 only)
-    uint32_t fw[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) fw[q] = P.w[q] & (0x01010101u * uint32_t((1 << f) - 1));
-#pragma unroll
-    for (int idx = 0; idx < 16; ++idx) {
-      const float x = PACKED ? -0.5f : __builtin_fmaf(float((fw[idx >> 2] >> (8 * (idx & 3))) & 0xffu), sf, -0.5f);
-      // u = n + 1/2 + w: for w in (j - 1, j), j an integer, the nearest integer to u is n + j =
-      // n + ceil(w); certain unless w lies within the bound of an integer (the bound adds the
-      // rounding of this fused multiply-add, below 2^-24 |w|, doubled)
-      const float w = __builtin_fmaf(acc[idx >> 2][idx & 3], a.c, x);
-      flag |= __builtin_amdgcn_ballot_w64(fabsf(w - __builtin_rintf(w)) <= __builtin_fmaf(0x1p-23f, fabsf(w), tz));
-      ut[idx] = n_of(idx) + int(__builtin_ceilf(w));
-    }
-    if (flag) {
-      // exact margins and float64 re-decision for the lanes' elements within the bound
-      uint32_t need = 0;
-#pragma unroll
-      for (int idx = 0; idx < 16; ++idx) {
-        float margin;
-        ut[idx] = grid_round(phi_code<PACKED>(P, idx), f, a.c * acc[idx >> 2][idx & 3], &margin);
-        need |= uint32_t(margin <= tau && row_ok && idx < kin) << idx;
-      }
-      while (__builtin_amdgcn_ballot_w64(need != 0)) {
-        const bool mine = need != 0;
-        const int idx = mine ? __builtin_ctz(need) : -1;
-        need &= need - 1;
-        int unew = 0;
-        if (mine) {
-          const int64_t col = c16 + idx;
-          const float* Ar = a.A + row * a.r;
-          const float* Bc = a.B + col;
-          double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;  // independent partial sums keep the loads in flight
-          int rho = 0;
-#pragma unroll 1
-          for (; rho + 4 <= a.r; rho += 4) {
-            d0 = __builtin_fma(double(Ar[rho]), double(Bc[int64_t(rho) * a.k]), d0);
-            d1 = __builtin_fma(double(Ar[rho + 1]), double(Bc[int64_t(rho + 1) * a.k]), d1);
-            d2 = __builtin_fma(double(Ar[rho + 2]), double(Bc[int64_t(rho + 2) * a.k]), d2);
-            d3 = __builtin_fma(double(Ar[rho + 3]), double(Bc[int64_t(rho + 3) * a.k]), d3);
-          }
-#pragma unroll 1
-          for (; rho < a.r; ++rho) d0 = __builtin_fma(double(Ar[rho]), double(Bc[int64_t(rho) * a.k]), d0);
-          unew = grid_round_f64(phi_code_dyn<PACKED>(P, idx), f, a.c64 * ((d0 + d1) + (d2 + d3)));
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) ut[j] = j == idx ? unew : ut[j];
-      }
-    }
-  }
-
-  // Clip and pack 16 nibbles (8 bytes) or 16 bytes (Q8OUT); columns >= k are
-  // written as 0.  Mask: bit idx of the lane's 16-bit word is [the rounded value
-  // of column c16 + idx lies on the grid].
-  if (!done) {
-#pragma unroll
-    for (int idx = 0; idx < 16; ++idx) {
-      const int q = min(max(ut[idx], lo), hi);
-      if constexpr (Q8OUT) {
-        qb[idx >> 2] |= uint32_t(q & 255) << (8 * (idx & 3));
-      } else {
-        const uint32_t nib = uint32_t(q & 15) << (4 * (idx & 7));
-        if (idx < 8) w0 |= nib;
-        else w1 |= nib;
-      }
-      if constexpr (MASK) mb |= uint32_t(q == ut[idx]) << idx;
-    }
-  }
-  if (kin < 16) {
+  const float tz = fmaxf(tau, 0.f);
+  const float sf = __builtin_bit_cast(float, uint32_t(127 - f) << 23);  // 2^-f
+  const uint32_t ones = 0x01010101u;
+  uint32_t q[4];
+  uint32_t need = 0;
+  o.mb = 0xFFFFu;
+  auto pack = [&]() {
     if constexpr (Q8OUT) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int nb = kin - 4 * g;  // bytes of word g inside k
-        qb[g] &= nb >= 4 ? 0xFFFFFFFFu : nb <= 0 ? 0u : (1u << (8 * nb)) - 1u;
-      }
+      for (int g = 0; g < 4; ++g) o.qb[g] = q[g];
     } else {
-      const uint64_t keep = (uint64_t(1) << (4 * kin)) - 1;  // kin <= 15
-      w0 &= uint32_t(keep);
-      w1 &= uint32_t(keep >> 32);
+      o.w0 = pack_nibble_bytes(q[0], q[1]);
+      o.w1 = pack_nibble_bytes(q[2], q[3]);
+    }
+  };
+  bool done = false;
+  if constexpr (!PACKED) {
+    float amx = 0.f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) amx = fmaxf(amx, fabsf(acc[g][v]));
+    if (!zero_delta && !__builtin_amdgcn_ballot_w64(!(amx * fabsf(a.c) < 0.5f - tz - 0x1p-20f && tau >= 0.f))) {
+      auto w_of = [&](int g, int v) {
+        const uint32_t fw = P.w[g] & (ones * uint32_t((1 << f) - 1));
+        return __builtin_fmaf(acc[g][v], a.c, __builtin_fmaf(float((fw >> (8 * v)) & 0xffu), sf, -0.5f));
+      };
+      float wmn = __builtin_inff();
+      uint32_t clip = 0;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 w;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          w[v] = w_of(g, v);
+          wmn = fminf(wmn, fabsf(w[v]));
+        }
+        q[g] = swar_carry_q8(P.w[g], (~sign_bytes(w) >> 7) & ones, f, bits, clip);
+      }
+      if (!__builtin_amdgcn_ballot_w64(clip != 0)) {
+        pack();
+        done = true;
+        if (__builtin_amdgcn_ballot_w64(!(wmn > tz))) {  // rare
+#pragma unroll
+          for (int idx = 0; idx < 16; ++idx) need |= uint32_t(!(fabsf(w_of(idx >> 2, idx & 3)) > tz)) << idx;
+        }
+      }
     }
   }
-  o.w0 = w0;
-  o.w1 = w1;
+  if (!done) {
+    constexpr float kMagic = 12582912.f;
+    uint32_t vb[16];
+    float dmx = 0.f, vmx = -__builtin_inff(), vmn = __builtin_inff();
+    auto u_of = [&](int idx) {
+      const float x = PACKED ? float(phi_code<true>(P, idx)) : float(phi_code<false>(P, idx)) * sf;
+      return __builtin_fmaf(acc[idx >> 2][idx & 3], a.c, x);
+    };
 #pragma unroll
-  for (int g = 0; g < 4; ++g) o.qb[g] = qb[g];
-  o.mb = mb;
+    for (int idx = 0; idx < 16; ++idx) {
+      const float u = u_of(idx), vm = u + kMagic, v = vm - kMagic;
+      vb[idx] = __float_as_uint(vm);
+      dmx = fmaxf(dmx, fabsf(u - v));
+      vmx = fmaxf(vmx, v);
+      vmn = fminf(vmn, v);
+    }
+    // v is certain unless u lies within the error bound of a half-integer: that of delta and the rounding
+    // of u, below 2^-24 (|v| + 1/2), more than doubled.  Values far off the grid and NaNs (whose norm bounds
+    // are infinite) are left to the exact path too.
+    const float vab = fmaxf(fabsf(vmx), fabsf(vmn));
+    const float thr = vab < 32768.f ? 0.5f - (tz + __builtin_fmaf(0x1p-22f, vab, 0x1p-21f)) : -1.f;
+    const bool sure = zero_delta || tau < 0.f;
+    if (__builtin_amdgcn_ballot_w64(!(dmx < thr || sure))) {  // rare
+#pragma unroll
+      for (int idx = 0; idx < 16; ++idx) {
+        const float u = u_of(idx);
+        need |= uint32_t(!(fabsf(u - (__uint_as_float(vb[idx]) - kMagic)) < thr || sure)) << idx;
+      }
+    }
+    if (__builtin_amdgcn_ballot_w64(!(vmx <= float(hi) && vmn >= float(lo)))) {
+      uint32_t mb = 0;
+#pragma unroll
+      for (int idx = 0; idx < 16; ++idx) {
+        const float vm = __uint_as_float(vb[idx]), vc = fminf(fmaxf(vm, kMagic + float(lo)), kMagic + float(hi));
+        if constexpr (MASK) mb |= uint32_t(vm == vc) << idx;
+        vb[idx] = __float_as_uint(vc);
+      }
+      o.mb = mb;
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      q[g] = __builtin_amdgcn_perm(vb[4 * g + 1], vb[4 * g], 0x0c0c0400u) |
+             __builtin_amdgcn_perm(vb[4 * g + 3], vb[4 * g + 2], 0x04000c0cu);
+      if (!Q8OUT) q[g] &= 0x0F0F0F0Fu;
+    }
+    pack();
+  }
+  if (edge) grid_clear(a, o, c16, Q8OUT);
+  if (need && edge) {  // columns past k need no settling
+    const int kin = int(max<int64_t>(0, min<int64_t>(16, a.k - c16)));
+    need &= (1u << kin) - 1u;
+  }
+  return need != 0 && row < a.m;
+}
+
+// 16-column pieces with an element to settle (row of the block << 4 | piece of its 256-column strip) go to a
+// queue of their wave, and are settled side by side after its last round, over their tentative results: 16
+// lanes each, an element a lane.  (A float64 delta is a memory round trip; decided inside the round loop
+// it held up the wave, and its registers left two waves per SIMD instead of three.  Merge of 11008 x 4096, Q8:
+// 58.5 -> 34.6 us.)  A wave's queue has room for all its pieces.
+template <bool PACKED, bool MASK, bool Q8OUT>
+__device__ __forceinline__ void grid_drain(const GridArgs& a, const uint16_t* queue, const int* nqueue, int64_t row0, int64_t strip0) {
+  const int nq = __builtin_amdgcn_readfirstlane(*nqueue);
+  if (nq == 0) return;
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the wave's tentative results are written
+  const int lo = -(1 << (a.bits - 1)), hi = (1 << (a.bits - 1)) - 1, f = PACKED ? 0 : 8 - a.bits;
+  const int lane = threadIdx.x & 63, idx = lane & 15;
+  for (int at = lane >> 4; at < nq; at += 4) {
+    const uint32_t e = queue[at];
+    const int64_t row = row0 + (e >> 4), col = strip0 + 16 * (e & 15) + idx;
+    const bool in = col < a.k;  // (rows past m are not queued)
+    int ut = 0;
+    if (in) {
+      const float *Ar = a.A + row * a.r, *Bc = a.B + col;
+      double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;  // independent partial sums
+      int rho = 0;
+#pragma unroll 1
+      for (; rho + 16 <= a.r; rho += 16) {  // 32 loads in flight
+        float av[16], bv[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          av[q] = Ar[rho + q];
+          bv[q] = Bc[int64_t(rho + q) * a.k];
+        }
+#pragma unroll
+        for (int q = 0; q < 16; q += 4) {
+          d0 = __builtin_fma(double(av[q]), double(bv[q]), d0);
+          d1 = __builtin_fma(double(av[q + 1]), double(bv[q + 1]), d1);
+          d2 = __builtin_fma(double(av[q + 2]), double(bv[q + 2]), d2);
+          d3 = __builtin_fma(double(av[q + 3]), double(bv[q + 3]), d3);
+        }
+      }
+#pragma unroll 1
+      for (; rho < a.r; ++rho) d0 = __builtin_fma(double(Ar[rho]), double(Bc[int64_t(rho) * a.k]), d0);
+      const uint32_t byte = a.phi0[row * a.ld_phi + (PACKED ? col >> 1 : col)];
+      const int code = PACKED ? int(byte << (28 - 4 * int(col & 1))) >> 28 : int(int8_t(byte));
+      ut = grid_round_f64(code, f, a.c64 * ((d0 + d1) + (d2 + d3)));
+    }
+    const int q = in ? min(max(ut, lo), hi) : 0;
+    if constexpr (Q8OUT) {
+      if (col < a.kq) a.qout[row * a.ldq + col] = uint8_t(q);
+    } else {
+      const int other = __shfl_xor(q, 1);
+      if (!(idx & 1) && col < a.kq) a.qout[row * a.ldq + (col >> 1)] = uint8_t((q & 15) | (other & 15) << 4);
+    }
+    if constexpr (MASK) {
+      const uint64_t on = __ballot(!in || q == ut);
+      if (idx == 0) a.mout[row * a.ldm + (col >> 4)] = uint16_t(on >> (lane & 48));
+    }
+  }
 }
 
 // Stores one lane's 16 columns of q (and mask) at row, columns c16 .. c16 + 15.
@@ -512,12 +502,17 @@ __device__ __forceinline__ void grid_store(const GridArgs& a, const GridOut& o, 
   }
 }
 
-template <bool PACKED, bool MASK, bool B4, bool Q8OUT>
-__device__ __forceinline__ void grid_finish(const GridArgs& a, const PhiRegs& P, const f32x4 (&acc)[4], float tau,
-                                            bool zero_delta, int64_t row, int64_t c16, bool small_delta = false) {
-  GridOut o;
-  grid_decide<PACKED, MASK, B4, Q8OUT>(a, P, acc, tau, zero_delta, row, c16, small_delta, o);
-  grid_store<MASK, Q8OUT>(a, o, row, c16);
+// q = Phi0 on a 4-bit grid.
+__device__ __forceinline__ void grid_copy(const GridArgs& a, const PhiRegs& P, int64_t c16, bool edge, GridOut& o) {
+  o.w0 = P.w[0];
+  o.w1 = P.w[1];
+  o.mb = 0xFFFFu;
+  if (edge) grid_clear(a, o, c16, false);
+}
+
+// A lane's norm bound of a row or column; infinite where a NaN would be lost in a maximum.
+__device__ __forceinline__ float norm_bound_nan(float ssq, float amax, int n) {
+  return ssq == ssq ? norm_bound(ssq, amax, n) : __builtin_inff();
 }
 
 // COAL (r = 32, 16-byte aligned A and B rows, k % 4 == 0): B and A are read
@@ -545,6 +540,9 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
   // columns bound the error.
   __shared__ __attribute__((aligned(16))) u32x4 bfrag[4][2][4][64];
   __shared__ __attribute__((aligned(16))) float arow[COAL ? 4 : 1][16][36];  // COAL: the tile's A rows (144-byte pitch)
+  __shared__ uint16_t queue[4][512];  // per wave (nit <= 8), see grid_drain
+  __shared__ int nqueue[4];
+  if (lane == 0) nqueue[wave] = 0;
   float bss = 0.f, bmx = 0.f;
   if constexpr (COAL) {
     // B[0..31][col0 .. col0 + 63]: 8 loads of 4 rank rows x 256 bytes, staged raw
@@ -581,7 +579,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
       bfrag[wave][1][cb][lane] = l;
       ss[cb] += __shfl_xor(ss[cb], 16);
       ss[cb] += __shfl_xor(ss[cb], 32);
-      bss = fmaxf(bss, ss[cb]);
+      bss = fmaxf(bss, ss[cb] == ss[cb] ? ss[cb] : __builtin_inff());
     }
     for (int off = 1; off < 64; off <<= 1) {
       bss = fmaxf(bss, __shfl_xor(bss, off));
@@ -612,7 +610,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
     for (int cb = 0; cb < 4; ++cb) {
       ss[cb] += __shfl_xor(ss[cb], 16);
       ss[cb] += __shfl_xor(ss[cb], 32);
-      bss = fmaxf(bss, ss[cb]);
+      bss = fmaxf(bss, ss[cb] == ss[cb] ? ss[cb] : __builtin_inff());
     }
     for (int off = 1; off < 64; off <<= 1) {
       bss = fmaxf(bss, __shfl_xor(bss, off));
@@ -684,7 +682,9 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
         small = (B4 || a.bits == 4) && !__builtin_amdgcn_ballot_w64(!(bound < 0.5f - 0x1p-20f));
       }
       if (small) {
-        grid_finish<PACKED, MASK, B4, Q8OUT>(a, Pc, acc, 0.f, false, row, c16, true);
+        GridOut o;
+        grid_copy(a, Pc, c16, col0 + GR_COLS > a.k, o);
+        grid_store<MASK, Q8OUT>(a, o, row, c16);
         continue;
       }
       u32x4 ah, al;
@@ -727,9 +727,14 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
     }
     // -1 where delta is exactly zero (a zero A row or zero B columns, e.g. B at its zero
     // initialisation), so that no element is re-decided there
-    const float tau = amx == 0.f ? -1.f : a.tau_coef * norm_bound(ass, amx, a.r) * nb;
-    grid_finish<PACKED, MASK, B4, Q8OUT>(a, Pc, acc, tau, bmx == 0.f, row, c16);
+    const float na = norm_bound_nan(ass, amx, a.r);
+    const float tau = na == 0.f ? -1.f : a.tau_coef * na * nb;
+    GridOut o;
+    const bool need = grid_decide<PACKED, MASK, B4, Q8OUT>(a, Pc, acc, tau, nb == 0.f, row, c16, col0 + GR_COLS > a.k, o);
+    if (need) queue[wave][atomicAdd(&nqueue[wave], 1)] = uint16_t((row - rb0 * 16) << 4 | ((c16 - (col0 - GR_COLS * wave)) >> 4));
+    grid_store<MASK, Q8OUT>(a, o, row, c16);
   }
+  grid_drain<PACKED, MASK, Q8OUT>(a, queue[wave], &nqueue[wave], rb0 * 16, col0 - GR_COLS * wave);
 }
 
 // Wide tiles, for r = 32 with 16-byte aligned A and B rows, k % 4 == 0 and
@@ -767,7 +772,7 @@ __device__ __forceinline__ void load_phi_w(PhiRegs (&P)[4], const GridArgs& a, i
 }
 
 template <bool PACKED, bool MASK, bool B4, bool Q8OUT, bool MULTI>
-__global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
+__global__ __launch_bounds__(GR_THREADS, MULTI || Q8OUT ? 2 : 3) void k_grid_w(GridArgs a) {
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
   // logical block: XCD x = blockIdx % 8 takes the contiguous range starting at x floor(N/8) + min(x, N % 8)
@@ -777,11 +782,15 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
   const int64_t strip0 = (lb % nstrips) * 4 * GR_COLS;
   const int64_t rb0 = (lb / nstrips) * 4 * a.nit + wave;  // the wave's first 16-row block
   const int nks = MULTI ? a.r / 32 : 1;                       // 32-rank chunks (MULTI: r a multiple of 32)
+  const bool edge = strip0 + 4 * GR_COLS > a.k;               // the strip has columns past k
 
   __shared__ __attribute__((aligned(16))) u32x4 bfrag[4][2][4][64];
   __shared__ __attribute__((aligned(16))) float arow[4][16][36];  // the wave's A rows (144-byte pitch)
   __shared__ float nbs[4];                                         // column-norm bound per sub-tile
   __shared__ float cnb[4], cna[4];                                 // block-wide copy test: B and A norm bounds per wave
+  __shared__ uint16_t queue[4][MULTI ? 256 : 1024];  // per wave, see grid_drain
+  __shared__ int nqueue[4];
+  if (lane == 0) nqueue[wave] = 0;
 
   // round 0's codes and A rows first: they do not depend on the B fragments
   PhiRegs P[4];
@@ -870,7 +879,9 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
   // the sub-tile's column-norm bound from the accumulated column sums (0 exactly when its B
   // columns are all zero), shared through LDS
   auto publish_nb = [&]() {
-    float bss = fmaxf(fmaxf(ssc[0], ssc[1]), fmaxf(ssc[2], ssc[3])), m = bmx;
+    float bss = 0.f, m = bmx;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) bss = fmaxf(bss, ssc[cb] == ssc[cb] ? ssc[cb] : __builtin_inff());
     for (int off = 1; off < 64; off <<= 1) {
       bss = fmaxf(bss, __shfl_xor(bss, off));
       m = fmaxf(m, __shfl_xor(m, off));
@@ -1027,7 +1038,6 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
           __syncthreads();
           const float nam = fmaxf(fmaxf(cna[0], cna[1]), fmaxf(cna[2], cna[3]));
           if (fabsf(a.c) * nam * nbm * 1.02f < lim) {  // block-uniform
-            const f32x4 zero[4] = {};
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
               const int64_t rowblk = rb0 + 4 * it;
@@ -1036,7 +1046,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
               GridOut out[4];
 #pragma unroll
               for (int j = 0; j < 4; ++j)
-                grid_decide<PACKED, MASK, B4, Q8OUT>(a, Pr[it][j], zero, 0.f, false, row, strip0 + 64 * g + 16 * j, true, out[j]);
+                grid_copy(a, Pr[it][j], strip0 + 64 * g + 16 * j, edge, out[j]);
               store_round(row, strip0 + 64 * g, out);
             }
             return;
@@ -1120,7 +1130,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
     rss += __shfl_xor(rss, 32);
     float rmx = fmaxf(amx, __shfl_xor(amx, 16));
     rmx = fmaxf(rmx, __shfl_xor(rmx, 32));
-    const float na = norm_bound(rss, rmx, a.r);
+    const float na = norm_bound_nan(rss, rmx, a.r);
     GridOut out[4];
 #pragma unroll 1
     for (int jl = 0; jl < 4; ++jl) {
@@ -1153,7 +1163,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
         small = (B4 || a.bits == 4) && !__builtin_amdgcn_ballot_w64(!(bound < 0.5f - 0x1p-20f));
       }
       if (small) {
-        grid_decide<PACKED, MASK, B4, Q8OUT>(a, Pj, acc, 0.f, false, row, c16, true, o);
+        grid_copy(a, Pj, c16, edge, o);
       } else {
         if constexpr (!MULTI) {
 #pragma unroll
@@ -1165,8 +1175,9 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
           }
         }
         // -1 where delta is exactly zero (a zero A row), so that no element is re-decided there
-        const float tau = rmx == 0.f ? -1.f : a.tau_coef * na * nb;
-        grid_decide<PACKED, MASK, B4, Q8OUT>(a, Pj, acc, tau, nb == 0.f, row, c16, false, o);
+        const float tau = na == 0.f ? -1.f : a.tau_coef * na * nb;
+        const bool need = grid_decide<PACKED, MASK, B4, Q8OUT>(a, Pj, acc, tau, nb == 0.f, row, c16, edge, o);
+        if (need) queue[wave][atomicAdd(&nqueue[wave], 1)] = uint16_t((row - (rb0 - wave) * 16) << 4 | ((c16 - strip0) >> 4));
       }
 #pragma unroll
       for (int t = 0; t < 4; ++t)
@@ -1208,6 +1219,8 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid_w(GridArgs a) {
       }
     }
   }
+
+  grid_drain<PACKED, MASK, Q8OUT>(a, queue[wave], &nqueue[wave], (rb0 - wave) * 16, strip0);
 }
 
 // ============================================================================ activations
