@@ -7,6 +7,7 @@ The functions keep the C names; tensors must be contiguous and on the GPU.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 
@@ -56,6 +57,14 @@ class LayerSpec:
     def c_struct(self) -> _Layer:
         return _Layer(self.out_features, self.in_features, self.rank, self.alpha, self.bits,
                       _FMT[self.phi_format], self.group_size, self.act_bits, _DT[self.act_dtype])
+
+    @functools.cached_property
+    def _c(self):
+        # the fields are frozen, so one struct serves every call (the library only reads it)
+        return self.c_struct()
+
+    def __getstate__(self):
+        return {k: v for k, v in self.__dict__.items() if k != "_c"}
 
     @property
     def torch_dtype(self):
@@ -141,27 +150,46 @@ def _check(status: int):
 
 
 def _ptr(t):
+    """Address of a tensor that _expect has passed (None: a null pointer)."""
+    return None if t is None else t.data_ptr()
+
+
+def _checked_ptr(t):
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
         raise TypeError("expected a torch.Tensor")
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("tensors passed to the LR-QAT library must be contiguous GPU tensors")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+# the current stream's handle without a Stream object around it, where torch offers that
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _torch_stream(stream):
     return torch.cuda.current_stream() if stream is None else stream
 
 
+_Tensor = torch.Tensor
+
+
 def _expect(t, shape, dtype, name, device=None):
     """Reject a tensor whose shape, dtype, layout or device the C ABI would
     misread (the library sees only a pointer)."""
+    # one expression for the tensors that pass: a decoding step calls the library every few microseconds
+    if (isinstance(t, _Tensor) and t.dtype is dtype and t.shape == shape and t.is_cuda and t.is_contiguous()
+            and (device is None or t.device == device)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name}: expected a torch.Tensor, got {type(t).__name__}")
     if tuple(t.shape) != tuple(shape) or t.dtype != dtype:
@@ -183,7 +211,7 @@ def _weights(spec: "LayerSpec", phi0, s, A, B, device, z=None):
 
 
 def lrqat_forward_workspace_size(spec: LayerSpec, tokens: int) -> int:
-    L = spec.c_struct()
+    L = spec._c
     n = _lib().lrqat_forward_workspace_size(ctypes.byref(L), tokens)
     if n == 0:
         raise LRQATError(LRQAT_EINVAL, _lib().lrqat_last_error().decode())
@@ -191,7 +219,7 @@ def lrqat_forward_workspace_size(spec: LayerSpec, tokens: int) -> int:
 
 
 def lrqat_backward_workspace_size(spec: LayerSpec, tokens: int) -> int:
-    L = spec.c_struct()
+    L = spec._c
     n = _lib().lrqat_backward_workspace_size(ctypes.byref(L), tokens)
     if n == 0:
         raise LRQATError(LRQAT_EINVAL, _lib().lrqat_last_error().decode())
@@ -211,7 +239,7 @@ def lrqat_init_from_weights(spec: LayerSpec, W0: torch.Tensor, stream=None, asym
         s0 = torch.empty(spec.scale_shape(), dtype=torch.float32, device=W0.device)
         z0 = torch.empty(spec.scale_shape(), dtype=torch.int32, device=W0.device) if asymmetric else None
         phi0 = torch.empty(spec.phi_shape(), dtype=spec.phi_dtype, device=W0.device)
-    L = spec.c_struct()
+    L = spec._c
     _check(_lib().lrqat_init_from_weights(ctypes.byref(L), _ptr(W0), _ptr(s0), _ptr(z0), _ptr(phi0), _stream(st)))
     return (s0, z0, phi0) if asymmetric else (s0, phi0)
 
@@ -223,7 +251,7 @@ def lrqat_init_lp(spec: LayerSpec, W0: torch.Tensor, p: float, n_grid: int = 100
     with torch.cuda.stream(st):
         s0 = torch.empty(spec.scale_shape(), dtype=torch.float32, device=W0.device)
         phi0 = torch.empty(spec.phi_shape(), dtype=spec.phi_dtype, device=W0.device)
-    L = spec.c_struct()
+    L = spec._c
     _check(_lib().lrqat_init_lp(ctypes.byref(L), _ptr(W0), float(p), int(n_grid), _ptr(s0), _ptr(phi0), _stream(st)))
     return s0, phi0
 
@@ -234,7 +262,7 @@ def lrqat_init_loftq(spec: LayerSpec, W0: torch.Tensor, s0: torch.Tensor, n_iter
     _expect(W0, (m, k), torch.float32, "W0")
     dev = W0.device
     _expect(s0, spec.scale_shape(), torch.float32, "s0", dev)
-    L = spec.c_struct()
+    L = spec._c
     n = _lib().lrqat_init_loftq_workspace_size(ctypes.byref(L))
     if n == 0:
         raise LRQATError(LRQAT_EINVAL, _lib().lrqat_last_error().decode())
@@ -257,17 +285,17 @@ def lrqat_forward(spec: LayerSpec, X, phi0, s, A, B, Y=None, ws=None, stream=Non
     _expect(X, (T, spec.in_features), spec.torch_dtype, "X")
     dev = X.device
     _weights(spec, phi0, s, A, B, dev, z)
-    st = _torch_stream(stream)
-    with torch.cuda.stream(st):  # buffers made here belong to the stream the kernels run on
-        if Y is None:
-            Y = torch.empty((T, spec.out_features), dtype=spec.torch_dtype, device=dev)
-        if ws is None:
-            ws = workspace(lrqat_forward_workspace_size(spec, T), dev)
+    if Y is None or ws is None:
+        with torch.cuda.stream(_torch_stream(stream)):  # buffers made here belong to the stream the kernels run on
+            if Y is None:
+                Y = torch.empty((T, spec.out_features), dtype=spec.torch_dtype, device=dev)
+            if ws is None:
+                ws = workspace(lrqat_forward_workspace_size(spec, T), dev)
     _expect(Y, (T, spec.out_features), spec.torch_dtype, "Y", dev)
     _expect(ws, (ws.numel(),), torch.uint8, "ws", dev)
-    L = spec.c_struct()
+    L = spec._c
     _check(_lib().lrqat_forward(ctypes.byref(L), T, _ptr(X), _ptr(phi0), _ptr(s), _ptr(z), _ptr(A), _ptr(B),
-                                _ptr(Y), _ptr(ws), ws.numel(), _stream(st)))
+                                _ptr(Y), _ptr(ws), ws.numel(), _stream(stream)))
     return Y
 
 
@@ -278,39 +306,38 @@ def _backward_args(spec, X, phi0, s, A, B, dY, dX, dA, dB, want_dx, ds, want_ds,
     dev = X.device
     _weights(spec, phi0, s, A, B, dev, z)
     _expect(dY, (T, m), spec.torch_dtype, "dY", dev)
-    st = _torch_stream(stream)
-    with torch.cuda.stream(st):  # buffers made here belong to the stream the kernels run on
-        if dX is None and want_dx:
-            dX = torch.empty((T, k), dtype=spec.torch_dtype, device=dev)
-        if dA is None:
-            dA = torch.empty((m, r), dtype=torch.float32, device=dev)
-        if dB is None:
-            dB = torch.empty((r, k), dtype=torch.float32, device=dev)
-        if ds is None and want_ds:
-            ds = torch.empty(spec.scale_shape(), dtype=torch.float32, device=dev)
+    if dA is None or dB is None or (dX is None and want_dx) or (ds is None and want_ds):
+        with torch.cuda.stream(_torch_stream(stream)):  # buffers made here belong to the stream the kernels run on
+            if dX is None and want_dx:
+                dX = torch.empty((T, k), dtype=spec.torch_dtype, device=dev)
+            if dA is None:
+                dA = torch.empty((m, r), dtype=torch.float32, device=dev)
+            if dB is None:
+                dB = torch.empty((r, k), dtype=torch.float32, device=dev)
+            if ds is None and want_ds:
+                ds = torch.empty(spec.scale_shape(), dtype=torch.float32, device=dev)
     if dX is not None:
         _expect(dX, (T, k), spec.torch_dtype, "dX", dev)
     _expect(dA, (m, r), torch.float32, "dA", dev)
     _expect(dB, (r, k), torch.float32, "dB", dev)
     if ds is not None:
         _expect(ds, spec.scale_shape(), torch.float32, "ds", dev)
-    return T, dev, st, dX, dA, dB, ds
+    return T, dev, dX, dA, dB, ds
 
 
 def lrqat_backward(spec: LayerSpec, X, phi0, s, A, B, dY, dX=None, dA=None, dB=None, want_dx=True,
                    accumulate=False, ws=None, stream=None, z=None, ds=None, want_ds=False):
     """-> (dX or None, dA, dB) with the straight-through estimator; W_hat is
     recomputed.  With want_ds (or a ds tensor) -> (dX, dA, dB, ds)."""
-    T, dev, st, dX, dA, dB, ds = _backward_args(spec, X, phi0, s, A, B, dY, dX, dA, dB, want_dx, ds, want_ds, z,
-                                                stream)
+    T, dev, dX, dA, dB, ds = _backward_args(spec, X, phi0, s, A, B, dY, dX, dA, dB, want_dx, ds, want_ds, z, stream)
     if ws is None:
-        with torch.cuda.stream(st):
+        with torch.cuda.stream(_torch_stream(stream)):
             ws = workspace(lrqat_backward_workspace_size(spec, T), dev)
     _expect(ws, (ws.numel(),), torch.uint8, "ws", dev)
-    L = spec.c_struct()
+    L = spec._c
     _check(_lib().lrqat_backward(ctypes.byref(L), T, _ptr(X), _ptr(phi0), _ptr(s), _ptr(z), _ptr(A), _ptr(B),
                                  _ptr(dY), _ptr(dX), _ptr(dA), _ptr(dB), _ptr(ds), int(bool(accumulate)), _ptr(ws),
-                                 ws.numel(), _stream(st)))
+                                 ws.numel(), _stream(stream)))
     return (dX, dA, dB, ds) if ds is not None else (dX, dA, dB)
 
 
@@ -318,12 +345,11 @@ def lrqat_backward_static(spec: LayerSpec, X, phi0, s, A, B, dY, dX, dA, dB, acc
                           z=None, ds=None):
     """lrqat_backward on the library's device-resident scratch array: every
     output tensor is the caller's, nothing is allocated."""
-    T, dev, st, dX, dA, dB, ds = _backward_args(spec, X, phi0, s, A, B, dY, dX, dA, dB, dX is not None, ds,
-                                                False, z, stream)
-    L = spec.c_struct()
+    T, dev, dX, dA, dB, ds = _backward_args(spec, X, phi0, s, A, B, dY, dX, dA, dB, dX is not None, ds, False, z, stream)
+    L = spec._c
     _check(_lib().lrqat_backward_static(ctypes.byref(L), T, _ptr(X), _ptr(phi0), _ptr(s), _ptr(z), _ptr(A),
                                         _ptr(B), _ptr(dY), _ptr(dX), _ptr(dA), _ptr(dB), _ptr(ds),
-                                        int(bool(accumulate)), _stream(st)))
+                                        int(bool(accumulate)), _stream(stream)))
     return (dX, dA, dB, ds) if ds is not None else (dX, dA, dB)
 
 
@@ -338,18 +364,17 @@ def lrqat_merge_to_int4(spec: LayerSpec, phi0, A, B, out=None, stream=None):
     _expect(phi0, spec.phi_shape(), spec.phi_dtype, "phi0", dev)
     _expect(A, (m, r), torch.float32, "A", dev)
     _expect(B, (r, k), torch.float32, "B", dev)
-    st = _torch_stream(stream)
     if out is None:
-        with torch.cuda.stream(st):
+        with torch.cuda.stream(_torch_stream(stream)):
             out = torch.empty((m, k // 2), dtype=torch.uint8, device=dev)
     _expect(out, (m, k // 2), torch.uint8, "out", dev)
-    L = spec.c_struct()
-    _check(_lib().lrqat_merge_to_int4(ctypes.byref(L), _ptr(phi0), _ptr(A), _ptr(B), _ptr(out), _stream(st)))
+    L = spec._c
+    _check(_lib().lrqat_merge_to_int4(ctypes.byref(L), _ptr(phi0), _ptr(A), _ptr(B), _ptr(out), _stream(stream)))
     return out
 
 
 def lrqat_infer_workspace_size(spec: LayerSpec, tokens: int) -> int:
-    L = spec.c_struct()
+    L = spec._c
     n = _lib().lrqat_infer_workspace_size(ctypes.byref(L), tokens)
     if n == 0:
         raise LRQATError(LRQAT_EINVAL, _lib().lrqat_last_error().decode())
@@ -366,17 +391,17 @@ def lrqat_infer_forward(spec: LayerSpec, X, W_int4, s, z=None, Y=None, ws=None, 
     _expect(s, spec.scale_shape(), torch.float32, "s", dev)
     if z is not None:
         _expect(z, spec.scale_shape(), torch.int32, "z", dev)
-    st = _torch_stream(stream)
-    with torch.cuda.stream(st):
-        if Y is None:
-            Y = torch.empty((T, m), dtype=spec.torch_dtype, device=dev)
-        if ws is None:
-            ws = workspace(lrqat_infer_workspace_size(spec, T), dev)
+    if Y is None or ws is None:
+        with torch.cuda.stream(_torch_stream(stream)):
+            if Y is None:
+                Y = torch.empty((T, m), dtype=spec.torch_dtype, device=dev)
+            if ws is None:
+                ws = workspace(lrqat_infer_workspace_size(spec, T), dev)
     _expect(Y, (T, m), spec.torch_dtype, "Y", dev)
     _expect(ws, (ws.numel(),), torch.uint8, "ws", dev)
-    L = spec.c_struct()
+    L = spec._c
     _check(_lib().lrqat_infer_forward(ctypes.byref(L), T, _ptr(X), _ptr(W_int4), _ptr(s), _ptr(z), _ptr(Y),
-                                      _ptr(ws), ws.numel(), _stream(st)))
+                                      _ptr(ws), ws.numel(), _stream(stream)))
     return Y
 
 
@@ -402,17 +427,16 @@ def lrqat_adamw_step(groups, step, total_steps, warmup_steps, beta1=0.9, beta2=0
     receiving the norm before clipping."""
     arr, dev = _groups(groups)
     cfg = _AdamWConfig(beta1, beta2, eps, max_grad_norm, int(total_steps), int(warmup_steps))
-    st = _torch_stream(stream)
     if ws is None:
         n = _lib().lrqat_adamw_workspace_size(len(groups), arr)
         if n == 0:
             raise LRQATError(LRQAT_EINVAL, _lib().lrqat_last_error().decode())
-        with torch.cuda.stream(st):
+        with torch.cuda.stream(_torch_stream(stream)):
             ws = workspace(n, dev or "cuda")
     if grad_norm is not None:
         _expect(grad_norm, (1,), torch.float32, "grad_norm", dev)
-    _check(_lib().lrqat_adamw_step(ctypes.byref(cfg), int(step), len(groups), arr, _ptr(grad_norm), _ptr(ws),
-                                   ws.numel(), _stream(st)))
+    _check(_lib().lrqat_adamw_step(ctypes.byref(cfg), int(step), len(groups), arr, _ptr(grad_norm), _checked_ptr(ws),
+                                   ws.numel(), _stream(stream)))
 
 
 def lrqat_timing_enable(on: bool = True):
