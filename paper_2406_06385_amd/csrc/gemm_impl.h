@@ -454,7 +454,9 @@ __device__ __forceinline__ void load_ks_bf16(RegsKs<AL>& R, const uint16_t* __re
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     if (e < w0 || e >= w1) continue;
-    const uint32_t off = (base + e * step) & (AL == kAlOdd && (e & 1) ? ~3u : ~0u);
+    // a K-line past the end must read zeros: with an odd count of elements the first one's leading dword
+    // holds the last element and two bytes beyond the tensor
+    const uint32_t off = AL == kAlOdd ? (k0 + 8 * kg + e < K ? (base + e * step) & ~3u : 0xFFFFFF00u) : base + e * step;
     R.v[e] = ld128(r, off);
     if constexpr (AL == kAlOdd)
       if (e & 1) R.x[e >> 1] = ld32(r, off + 16);
