@@ -23,19 +23,19 @@ def lr():
 
 CASES = [
     # m, k, T, r, bits, fmt, g, act, asym
-    (129, 255, 257, 8, 4, "q8", 0, 0, False),            # odd rows everywhere, one past the 128-row tiles
-    (130, 258, 130, 5, 4, "int_packed2", 0, 0, True),    # rows on dwords, a partial K-tile, zero offset
-    (131, 320, 200, 32, 6, "q8", 0, 0, False),           # m odd (dX, dW rows), k a whole number of K-tiles
-    (192, 323, 192, 16, 3, "q8", 0, 0, False),           # k odd, m aligned
+    (129, 255, 513, 8, 4, "q8", 0, 0, False),            # odd rows everywhere, one past the 128-row tiles
+    (130, 258, 514, 5, 4, "int_packed2", 0, 0, True),    # rows on dwords, a partial K-tile, zero offset
+    (131, 320, 520, 32, 6, "q8", 0, 0, False),           # m odd (dX, dW rows), k a whole number of K-tiles
+    (192, 323, 576, 16, 3, "q8", 0, 0, False),           # k odd, m aligned
     (256, 1030, 1300, 20, 4, "int_packed2", 0, 0, False),  # dW split over the tokens, unaligned rows
     (264, 512, 2050, 33, 4, "q8", 128, 0, True),         # dW split with a short last part, groups with offsets
     (256, 4096, 2048, 4, 4, "int_packed2", 0, 0, False),  # dX in 256 x 128 tiles
     (128, 11008, 640, 4, 4, "int_packed2", 0, 0, False),  # dX in 128 x 256 tiles
     (4096, 128, 2048, 4, 4, "q8", 0, 0, False),          # forward in 256 x 128 tiles
-    (320, 640, 300, 8, 4, "int_packed2", 0, 8, True),    # int8 forward with a zero offset
-    (257, 384, 129, 8, 6, "q8", 0, 8, True),             # int8 forward on an int8 grid, one token past the small kernel
-    (136, 1000, 200, 8, 4, "int_packed2", 0, 8, False),  # int8 forward, k no multiple of its 128-value K-tile
-    (136, 640, 200, 8, 4, "q8", 64, 8, False),           # int8 tokens widened (group-wise scales)
+    (320, 640, 530, 8, 4, "int_packed2", 0, 8, True),    # int8 forward with a zero offset
+    (257, 384, 600, 8, 6, "q8", 0, 8, True),             # int8 forward on an int8 grid
+    (136, 1000, 520, 8, 4, "int_packed2", 0, 8, False),  # int8 forward, k no multiple of its 128-value K-tile
+    (136, 640, 520, 8, 4, "q8", 64, 8, False),           # int8 tokens widened (group-wise scales)
 ]
 
 
@@ -51,7 +51,7 @@ def test_tiles(lr, case):
 def test_nan_stays_in_its_rows(lr):
     """Rows that are not 16-byte aligned are loaded past their end (into the next row) and masked: a NaN at
     the start of a row must not reach the row before it."""
-    c = Layer(lr, 140, 201, 160, 8, 8.0, 4, "q8", 0, 0, "bf16", seed=77)
+    c = Layer(lr, 140, 201, 560, 8, 8.0, 4, "q8", 0, 0, "bf16", seed=77)
     X, dY = c.d_X.clone(), c.d_dY.clone()
     ref = lr.lrqat_forward(c.spec, c.d_X, c.d_phi, c.d_s, c.d_A, c.d_B)
     base = lr.lrqat_backward(c.spec, c.d_X, c.d_phi, c.d_s, c.d_A, c.d_B, c.d_dY)
@@ -60,9 +60,24 @@ def test_nan_stays_in_its_rows(lr):
     Y = lr.lrqat_forward(c.spec, X, c.d_phi, c.d_s, c.d_A, c.d_B)
     got = lr.lrqat_backward(c.spec, c.d_X, c.d_phi, c.d_s, c.d_A, c.d_B, dY)
     torch.cuda.synchronize()
-    keep = [t for t in range(160) if t != 50]
+    keep = [t for t in range(560) if t != 50]
     assert torch.equal(Y[keep], ref[keep]) and Y[50].isnan().all()
-    keep = [t for t in range(160) if t != 61]
+    keep = [t for t in range(560) if t != 61]
     assert torch.equal(got[0][keep], base[0][keep])
     rows = list(range(8, 140))
     assert torch.equal(got[1][rows], base[1][rows])
+
+
+@pytest.mark.parametrize("m,k,T", [(129, 255, 513), (131, 320, 577), (256, 323, 321)])
+def test_bytes_past_a_tensor_stay_out(lr, m, k, T):
+    """An odd number of bfloat16 elements ends in the middle of a dword; the vector loads read that
+    dword whole, and the two bytes past the tensor (NaNs here) must not enter any sum."""
+    c = Layer(lr, m, k, T, 8, 8.0, 4, "q8", 0, 0, "bf16", seed=91)
+
+    def tight(x):
+        buf = torch.full((x.numel() + 64,), float("nan"), dtype=x.dtype, device="cuda")
+        buf[: x.numel()] = x.flatten()
+        return buf[: x.numel()].view(x.shape)
+
+    c.d_X, c.d_dY = tight(c.d_X), tight(c.d_dY)
+    check_layer(lr, c)
