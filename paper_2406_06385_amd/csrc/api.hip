@@ -252,7 +252,7 @@ lrqat_status weight_gemm_forward(const Dims& d, int64_t tokens, const void* X, c
   p.nsum = d.act ? nsum : nullptr;
   p.out = Y; p.ldo = d.m;
   p.plan = gemm_plan(kFwd, d.act, d.g != 0, gemm_al16(kFwd, d.act, p.K, p.lda, p.ldb), p.M, p.N, p.K);
-  if (tokens <= kSmallTokens)
+  if (fwd_small(tokens, d.m))
     return hip_status(timed("gemm_fwd", st, [&] { return launch_fwd_small(d.act, d.g != 0, d.q8w, p, st); }), "gemm_fwd");
   const int opt = (z ? kOptZ : 0) | (d.q8w ? kOptQ8 : 0);
   return hip_status(timed("gemm_fwd", st, [&] { return launch_gemm(kFwd, d.act, d.g != 0, opt, p, st); }), "gemm_fwd");
@@ -615,7 +615,7 @@ lrqat_status lrqat_infer_forward(const lrqat_layer* layer, int64_t tokens, const
   const uint8_t* q = W_int4;
   int64_t ldq = d.k / 2;
   // (the few-token kernel reads rows at any alignment)
-  if (d.k % 32 && !(d.bf16 && tokens <= kSmallTokens)) {
+  if (d.k % 32 && !(d.bf16 && fwd_small(tokens, d.m))) {
     // rows of k/2 bytes are not 16-byte aligned: copy them into zero-padded rows of kpad/2 bytes
     uint8_t* qp = base + w.q;
     LRQAT_TRY(hip_status(timed("infer_relayout", st, [&] {

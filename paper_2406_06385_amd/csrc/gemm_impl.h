@@ -214,6 +214,9 @@ __device__ __forceinline__ void store_q_kc_one(uint16_t* tile, const RegsQKc<NH>
   const int row = (t >> 1) + 128 * i;
   const uint32_t w = R.v[i][c];
   u32x4 o;
+  if constexpr (!GRP && !ZP) {
+    o = unpack_q16(w);  // q / 16: the epilogue's scale has the factor back
+  } else
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     int na = nibble(w, 2 * q), nb = nibble(w, 2 * q + 1);
@@ -773,14 +776,16 @@ void k_gemm(GemmArgs p) {
   if constexpr (V == kFwd || V == kDx) {
     uint16_t* out = static_cast<uint16_t*>(p.out);
     const int64_t col_l = n0 + wn + 4 * (lane >> 5);
-    f32x4 cs[NJ][4];  // per-channel forward scales of the lane's columns
+    // per-channel forward scales of the lane's columns (packed q without zero offsets entered as q / 16)
+    constexpr float kQScale = V == kFwd && !GRP && (OPT & (kOptZ | kOptQ8)) == 0 && ACT != kActI8 ? 16.f : 1.f;
+    f32x4 cs[NJ][4];
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int64_t c = col_l + 32 * j + 8 * g;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) cs[j][g][e] = (V == kFwd && !GRP && c + e < p.N) ? p.s[c + e] : 1.f;
+        for (int e = 0; e < 4; ++e) cs[j][g][e] = (V == kFwd && !GRP && c + e < p.N) ? p.s[c + e] * kQScale : 1.f;
       }
     // The tile goes through LDS (bf16 [BM][BN], 16-byte chunks permuted by row
     // as in g_off) and back to memory as whole row segments: a store

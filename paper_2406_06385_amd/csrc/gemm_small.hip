@@ -16,10 +16,10 @@
 // sums of integer products are exact in int32, s and s_x are applied once at
 // the end, and a zero offset as (sum n q) - z (sum n).
 //
-// Measured (HIP-graph replays, weights of several layers in turn; the general
-// GEMM -> this kernel), bf16 tokens: 4096 x 4096, T = 1 84 -> 8.1 us, T = 128
-// 84 -> 49 us; 14336 x 4096, T = 32 85 -> 37 us, T = 128 86 -> 72 us; int8 tokens
-// with their quantisation: 14336 x 4096, T = 24 104 -> 24 us, T = 128 105 -> 43 us.
+// Measured (HIP-graph replays, weights of several layers in turn; 256 x 256 tiles
+// -> this kernel), bf16 tokens: 4096 x 4096, T = 1 84 -> 7.2 us, T = 128 84 -> 26;
+// 14336 x 4096, T = 1 85 -> 18, T = 64 86 -> 39; int8 tokens with their
+// quantisation: 14336 x 4096, T = 24 104 -> 18, 4096 x 14336, T = 128 331 -> 45.
 #include "gemm_impl.h"
 
 namespace lrqat {
@@ -56,6 +56,7 @@ __global__ __launch_bounds__(1024) void k_small(GemmArgs p) {
   const int64_t n0 = int64_t(blockIdx.x) * 16 * RG, t0 = int64_t(blockIdx.y) * 16 * TG;
   const int nch = int((p.K + 127) / 128);
   constexpr int NQ = Q8 ? 2 : 1;           // 16-byte loads of q per lane and chunk
+  constexpr bool Q16 = MODE != kSmallI8 && !GRP && !Q8;  // without zero offsets q enters as q / 16
   constexpr int PF = RG * NQ * TG <= 2 ? 4 : 2;  // chunks whose weights are in flight together
 
   const auto rq = rsrc4(static_cast<const uint8_t*>(p.b) + n0 * p.ldb, (p.N - n0) * p.ldb);
@@ -134,6 +135,10 @@ __global__ __launch_bounds__(1024) void k_small(GemmArgs p) {
 #pragma unroll
         for (int w8 = 0; w8 < 4; ++w8) {
           u32x4 wv[RG];
+          if (Q16 && !p.z) {  // uniform
+#pragma unroll
+            for (int r = 0; r < RG; ++r) wv[r] = unpack_q16(qv[f][r][0][w8]);
+          } else
 #pragma unroll
           for (int r = 0; r < RG; ++r)
 #pragma unroll
@@ -202,7 +207,7 @@ __global__ __launch_bounds__(1024) void k_small(GemmArgs p) {
       f32x4 s = {0.f, 0.f, 0.f, 0.f};
       for (int w = 0; w < nw; ++w) s += red[(w * RG * TG + i) * 64 + lane];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) val[e] = s[e];
+      for (int e = 0; e < 4; ++e) val[e] = Q16 && !p.z ? 16.f * s[e] : s[e];
     }
     if (tok >= p.M) continue;
     const float rsx = MODE != kSmallBf16 ? p.sx[tok] : 1.f;
@@ -219,25 +224,27 @@ __global__ __launch_bounds__(1024) void k_small(GemmArgs p) {
   }
 }
 
-template <int MODE, bool GRP, bool Q8, int TG>
-hipError_t launch_tg(const GemmArgs& p, hipStream_t st) {
-  constexpr int RG = TG >= 4 ? 2 : 1;
+template <int MODE, bool GRP, bool Q8, int TG, int RG>
+hipError_t launch_rg(const GemmArgs& p, hipStream_t st) {
   const int64_t nb = (p.N + 16 * RG - 1) / (16 * RG), nt = (p.M + 16 * TG - 1) / (16 * TG), nch = (p.K + 127) / 128;
-  // waves per block: enough for eight waves on each of the 256 CUs, at most one per chunk of K,
-  // and at most 64 KiB of partial sums
+  // waves per block: enough for 16 waves on each of the 256 CUs (8 with more than 16 tokens: more only
+  // add partial sums), at most one per chunk of K, and at most 64 KiB of partial sums
   int64_t w = 4;
-  while (w < 16 && nb * nt * w < 2048 && 2 * w * RG * TG <= 64) w *= 2;
+  while (w < 16 && nb * nt * w < (TG == 1 ? 4096 : 2048) && 2 * w * RG * TG <= 64) w *= 2;
   while (w > 1 && w > nch) w /= 2;
   k_small<MODE, GRP, Q8, TG, RG><<<dim3(unsigned(nb), unsigned(nt)), unsigned(64 * w), size_t(w) * RG * TG * 1024, st>>>(p);
   return hipGetLastError();
 }
 
+// Token groups of 16 per block by the token count, four at most (eight held too many registers: 128
+// tokens through 4096 x 4096 took 51 us, 26 as two blocks of four).  A second row group halves the
+// token loads per weight: with four token groups, and with two where the rows still give 512 blocks
+// (14336 x 4096, T = 32 38 -> 25 us; 1024 x 4096 would lose blocks, 11.1 -> 12.1).
 template <int MODE, bool GRP, bool Q8>
 hipError_t launch_mode(const GemmArgs& p, hipStream_t st) {
-  if (p.M <= 16) return launch_tg<MODE, GRP, Q8, 1>(p, st);
-  if (p.M <= 32) return launch_tg<MODE, GRP, Q8, 2>(p, st);
-  if (p.M <= 64) return launch_tg<MODE, GRP, Q8, 4>(p, st);
-  return launch_tg<MODE, GRP, Q8, 8>(p, st);
+  if (p.M <= 16) return launch_rg<MODE, GRP, Q8, 1, 1>(p, st);
+  if (p.M <= 32) return p.N >= 8192 ? launch_rg<MODE, GRP, Q8, 2, 2>(p, st) : launch_rg<MODE, GRP, Q8, 2, 1>(p, st);
+  return launch_rg<MODE, GRP, Q8, 4, 2>(p, st);
 }
 
 }  // namespace

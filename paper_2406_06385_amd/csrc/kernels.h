@@ -110,11 +110,12 @@ hipError_t launch_dx_i4(bool grouped, bool zp, const GemmArgs& p, hipStream_t st
 hipError_t launch_dx_i8(bool grouped, bool zp, const GemmArgs& p, hipStream_t st);       // gemm_dx_q8.hip
 hipError_t launch_dw_pc(const GemmArgs& p, hipStream_t st);                              // gemm_dw.hip
 hipError_t launch_dw_grp(const GemmArgs& p, hipStream_t st);                             // gemm_dw_grp.hip
-// few tokens, weights streamed: gemm_small.hip.  At 128 tokens it is ahead of the
-// general GEMM on every layer measured (4096 x 4096 49 against 84 us, 4096 x 14336
-// 203 against 275, 14336 x 4096 72 against 86); past that its token groups start over
-// and read the weights twice.
-constexpr int64_t kSmallTokens = 128;
+// Few tokens: the weights streamed (gemm_small.hip) against the tiles of the general GEMM.  Up to 64 tokens
+// the streaming kernel reads them once and is ahead on every layer measured (14336 x 4096, T = 64: 39
+// against 45 us); past that each 64 tokens read them again, which pays while its blocks (32 rows by 64
+// tokens) are few: 1024 x 4096, T = 512 (256 blocks) 26 against 45 us, 4096 x 4096, T = 192 (384) 37 against 37,
+// T = 256 (512) 44 against 37, 14336 x 4096, T = 96 (896) 59 against 45.
+inline bool fwd_small(int64_t T, int64_t m) { return T <= 64 || (T <= 512 && ((m + 31) / 32) * ((T + 63) / 64) < 384); }
 hipError_t launch_fwd_small(bool act, bool grouped, bool q8, const GemmArgs& p, hipStream_t st);
 // rows of w bytes re-laid with a leading dimension of ldd bytes, zero-filled
 hipError_t launch_repack_rows(const uint8_t* src, int64_t m, int64_t w, uint8_t* dst, int64_t ldd, hipStream_t st);

@@ -1,6 +1,5 @@
-"""GPU parity of the few-token forward (T <= 128 tokens: weights streamed, K
-split over a block's waves), at the edges of its token groups (16, 32, 64,
-128), with partial row groups, partial K chunks and rows at every alignment,
+"""GPU parity of the few-token forward (weights streamed, K split over a
+block's waves), at the edges of its token groups (16, 32, 64) and past them, with partial row groups, partial K chunks and rows at every alignment,
 against the CPU oracle.  Tolerances as in test_gpu_parity: bfloat16 outputs and
 bfloat16 weight operands, 2e-2 by Frobenius norm and per line."""
 import numpy as np
@@ -35,7 +34,9 @@ CASES = [
     (80, 288, 128, 6, "q8", 32, 0, True),              # int8 grid, groups of one 32-column chunk
     (72, 520, 31, 7, "q8", 0, 0, False),               # int8 grid, per channel
     (640, 1030, 3, 4, "int_packed2", 0, 8, True),      # int8 tokens, int8 MFMA, zero offset
-    (160, 4096, 128, 4, "int_packed2", 0, 8, False),   # int8 tokens, largest token count
+    (160, 4096, 128, 4, "int_packed2", 0, 8, False),   # int8 tokens, two blocks of tokens
+    (200, 640, 511, 4, "q8", 0, 0, False),             # the most tokens, rows past m
+    (8200, 256, 20, 4, "int_packed2", 0, 0, False),    # two row groups with two token groups
     (96, 640, 64, 6, "q8", 0, 8, True),                # int8 tokens, int8 grid
     (96, 640, 40, 4, "q8", 64, 8, True),               # int8 tokens, group-wise scales (widened to bfloat16)
 ]
