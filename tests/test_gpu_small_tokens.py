@@ -73,3 +73,24 @@ def test_int8_sum_is_exact(lr):
     Y = lr.lrqat_forward(c.spec, c.d_X, c.d_phi, c.d_s, c.d_A, c.d_B, z=c.d_z)
     torch.cuda.synchronize()
     assert torch.equal(Y.cpu(), torch.from_numpy(ref.astype(np.float32)).to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("k", [40, 1002, 2048, 2056, 8200, 16384, 16408])
+def test_token_codes_at_every_row_length(lr, k):
+    """Row lengths on both sides of what the token quantisation holds in registers (2048, 4096, 8192 and 16384
+    values) and one that is no whole number of 16-byte vectors: the codes are exact, so Y is too, as above
+    (|N| <= 127 * 7 * k < 2^24)."""
+    c = Layer(lr, 32, k, 5, 4, 4.0, 4, "int_packed2", 0, 8, "bf16", seed=401, b_std=0.02)
+    X = c.Xv.copy()
+    X[1] = 0.0                  # a token of zeros
+    X[2, : k - 1] = 0.0         # its only value, and the maximum, in the last place
+    X[3, 0] = 64.0              # and in the first
+    d_X = torch.from_numpy(X.astype(np.float32)).to(torch.bfloat16).cuda()
+    X = d_X.float().cpu().numpy().astype(np.float64)
+    q, _, _, _ = O.grid_from_inputs(c.phi_ref, c.A, c.B, 4.0, 4, 4, "int_packed2")
+    _, n, sx = O.act_quant(X)
+    N = (n @ q.T).astype(np.float32)
+    ref = (N * c.s_ref[None, :].astype(np.float32)).astype(np.float32) * sx[:, None].astype(np.float32)
+    Y = lr.lrqat_forward(c.spec, d_X, c.d_phi, c.d_s, c.d_A, c.d_B)
+    torch.cuda.synchronize()
+    assert torch.equal(Y.cpu(), torch.from_numpy(ref.astype(np.float32)).to(torch.bfloat16))
