@@ -428,13 +428,13 @@ lrqat_status backward_impl(const lrqat_layer* layer, int64_t tokens, const void*
   for (int i = 0; i < 2; ++i) ra.vec[i] = ra.n[i] % 4 == 0 && aligned(ra.out[i], 16);
   ra.c = d.c;
   ra.accumulate = accumulate;
-  LRQAT_TRY(hip_status(timed("reduce", st, [&] { return launch_reduce2(ra, st); }), "reduce"));
   if (ds) {
-    const int64_t nchunks = (d.k + 31) / 32, cpg = d.g ? d.g / 32 : nchunks;
-    LRQAT_TRY(hip_status(timed("reduce_ds", st, [&] {
-                           return launch_reduce_ds(ds_part, d.m, d.kpad / 32, nchunks, cpg, d.ngroups, w.dw.split, ds, accumulate, st);
-                         }), "reduce_ds"));
+    ra.ds = ds; ra.ds_part = ds_part;
+    ra.m = d.m; ra.ldds = d.kpad / 32; ra.nchunks = (d.k + 31) / 32;
+    ra.cpg = d.g ? d.g / 32 : ra.nchunks;
+    ra.ngroups = d.ngroups; ra.nsplit = w.dw.split;
   }
+  LRQAT_TRY(hip_status(timed("reduce", st, [&] { return launch_reduce2(ra, st); }), "reduce"));
   return LRQAT_OK;
 }
 

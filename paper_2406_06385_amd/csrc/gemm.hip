@@ -17,10 +17,38 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ part, 
   out[idx] = (accumulate ? out[idx] : 0.f) + c * s;
 }
 
-// Both rank-r gradients in one launch: out = (accumulate ? out : 0) + c * sum_p part[p] for
-// dA (side 0) and dB (side 1).  Four consecutive elements per thread; the partial buffers
-// are summed in a fixed order (two interleaved running sums), so results are deterministic.
+// ds[row][grp] = (accumulate ? ds : 0) + the partials of the group's 32-column chunks over all splits.
+// 2^lg consecutive lanes share a (row, group): each takes every 2^lg-th chunk (coalesced), and their sums
+// meet in a fixed tree, so the result is deterministic.  (One thread per row, whose loads are a row apart,
+// took 47 us for 4096 rows of 344 chunks.)
+template <class I>
+__device__ __forceinline__ void reduce_ds(const Reduce2Args& ra, int64_t t) {
+  const int64_t idx = t >> ra.lg;
+  const bool in = idx < ra.m * ra.ngroups;
+  const int l = int(t & ((1 << ra.lg) - 1));
+  float s = 0.f;
+  if (in) {
+    const int64_t row = int64_t(I(idx) / I(ra.ngroups)), grp = idx - row * ra.ngroups;
+    const int64_t c0 = grp * ra.cpg, c1 = min(ra.nchunks, c0 + ra.cpg);
+    for (int q = 0; q < ra.nsplit; ++q) {
+      const float* src = ra.ds_part + (q * ra.m + row) * ra.ldds;
+      for (int64_t c = c0 + l; c < c1; c += int64_t(1) << ra.lg) s += src[c];
+    }
+  }
+  for (int off = (1 << ra.lg) >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  if (in && l == 0) ra.ds[idx] = (ra.accumulate ? ra.ds[idx] : 0.f) + s;
+}
+
+// The gradients of A, B and s in one launch: out = (accumulate ? out : 0) + c * sum_p part[p] for
+// dA (side 0) and dB (side 1), then the blocks of ds.  Four consecutive elements per thread; the partial
+// buffers are summed in a fixed order (two interleaved running sums), so results are deterministic.
 __global__ __launch_bounds__(256) void k_reduce2(Reduce2Args ra) {
+  if (int64_t(blockIdx.x) >= ra.nblocks) {  // block-uniform
+    const int64_t td = (int64_t(blockIdx.x) - ra.nblocks) * 256 + threadIdx.x;
+    if (ra.m * ra.ngroups < (int64_t(1) << 31)) reduce_ds<uint32_t>(ra, td);
+    else reduce_ds<int64_t>(ra, td);
+    return;
+  }
   const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
   const int64_t nt0 = (ra.n[0] + 3) / 4;
   const int side = t < nt0 ? 0 : 1;
@@ -53,9 +81,16 @@ __global__ __launch_bounds__(256) void k_reduce2(Reduce2Args ra) {
   }
 }
 
-hipError_t launch_reduce2(const Reduce2Args& ra, hipStream_t st) {
-  const int64_t nt = (ra.n[0] + 3) / 4 + (ra.n[1] + 3) / 4;
-  k_reduce2<<<unsigned((nt + 255) / 256), 256, 0, st>>>(ra);
+hipError_t launch_reduce2(const Reduce2Args& ra0, hipStream_t st) {
+  Reduce2Args ra = ra0;
+  ra.nblocks = ((ra.n[0] + 3) / 4 + (ra.n[1] + 3) / 4 + 255) / 256;
+  int64_t nds = 0;
+  if (ra.ds) {
+    ra.lg = 0;  // lanes per sum of ds: up to a wave, no more than its chunks
+    while (ra.lg < 6 && (int64_t(2) << ra.lg) <= ra.cpg) ++ra.lg;
+    nds = (((ra.m * ra.ngroups) << ra.lg) + 255) / 256;
+  }
+  k_reduce2<<<unsigned(ra.nblocks + nds), 256, 0, st>>>(ra);
   return hipGetLastError();
 }
 
@@ -119,40 +154,6 @@ hipError_t launch_gemm(GemmVariant v, bool act, bool grouped, int opt, const Gem
       return grouped ? launch_dw_grp(p, st) : launch_dw_pc(p, st);
   }
   return hipErrorInvalidValue;
-}
-
-// ds[row][grp] = (accumulate ? ds : 0) + the partials of the group's 32-column chunks over all splits.
-// 2^lg consecutive lanes share a (row, group): each takes every 2^lg-th chunk (coalesced), and their sums
-// meet in a fixed tree, so the result is deterministic.  (One thread per row, whose loads are a row apart,
-// took 47 us for 4096 rows of 344 chunks.)
-__global__ __launch_bounds__(256) void k_reduce_ds(const float* __restrict__ part, int64_t m, int64_t ldpart,
-                                                   int64_t nchunks, int64_t cpg, int64_t ngroups, int nsplit, int lg,
-                                                   float* __restrict__ ds, int accumulate) {
-  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x, idx = t >> lg;
-  const bool in = idx < m * ngroups;
-  const int l = int(t & ((1 << lg) - 1));
-  float s = 0.f;
-  if (in) {
-    const int64_t row = idx / ngroups, grp = idx % ngroups;
-    const int64_t c0 = grp * cpg, c1 = min(nchunks, c0 + cpg);
-    for (int q = 0; q < nsplit; ++q) {
-      const float* src = part + (q * m + row) * ldpart;
-      for (int64_t c = c0 + l; c < c1; c += int64_t(1) << lg) s += src[c];
-    }
-  }
-  for (int off = (1 << lg) >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off);
-  if (in && l == 0) ds[idx] = (accumulate ? ds[idx] : 0.f) + s;
-}
-
-hipError_t launch_reduce_ds(const float* part, int64_t m, int64_t ldpart, int64_t nchunks, int64_t chunks_per_group,
-                            int64_t ngroups, int nsplit, float* ds, int accumulate, hipStream_t st) {
-  const int64_t n = m * ngroups;
-  if (n == 0) return hipSuccess;
-  int lg = 0;  // lanes per sum: up to a wave, no more than its chunks
-  while (lg < 6 && (int64_t(2) << lg) <= chunks_per_group) ++lg;
-  k_reduce_ds<<<unsigned(((n << lg) + 255) / 256), 256, 0, st>>>(part, m, ldpart, nchunks, chunks_per_group, ngroups, nsplit,
-                                                                 lg, ds, accumulate);
-  return hipGetLastError();
 }
 
 // dst[row][0 .. ldd) = src[row][0 .. w) followed by zeros; one thread per destination byte.

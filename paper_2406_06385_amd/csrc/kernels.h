@@ -119,9 +119,6 @@ inline bool fwd_small(int64_t T, int64_t m) { return T <= 64 || (T <= 512 && ((m
 hipError_t launch_fwd_small(bool act, bool grouped, bool q8, const GemmArgs& p, hipStream_t st);
 // rows of w bytes re-laid with a leading dimension of ldd bytes, zero-filled
 hipError_t launch_repack_rows(const uint8_t* src, int64_t m, int64_t w, uint8_t* dst, int64_t ldd, hipStream_t st);
-// ds[row][grp] = (accumulate ? ds : 0) + sum of the 32-column chunk partials of the group
-hipError_t launch_reduce_ds(const float* part, int64_t m, int64_t ldpart, int64_t nchunks, int64_t chunks_per_group,
-                            int64_t ngroups, int nsplit, float* ds, int accumulate, hipStream_t st);
 hipError_t launch_reduce(const float* part, int64_t nparts, int64_t n, float* out, float c, int accumulate,
                          hipStream_t st);
 struct Reduce2Args {        // side 0: dA, side 1: dB
@@ -131,6 +128,13 @@ struct Reduce2Args {        // side 0: dA, side 1: dB
   int vec[2];               // 16-byte aligned rows and n % 4 == 0
   float c;
   int accumulate;
+  // ds[row][grp] (nullable) = (accumulate ? ds : 0) + the 32-column chunk partials [nsplit][m][ldds] of the group
+  float* ds;
+  const float* ds_part;
+  int64_t m, ldds, nchunks, cpg, ngroups;  // chunks of a row and of a group
+  int nsplit;
+  int lg;                   // set by launch_reduce2
+  int64_t nblocks;
 };
 hipError_t launch_reduce2(const Reduce2Args& ra, hipStream_t st);
 
