@@ -103,13 +103,13 @@ hipError_t launch_reduce2(const Reduce2Args& ra0, hipStream_t st) {
 // 49; dX of 2048 tokens through 14336 x 4096 (128 tiles) 339 -> 254.
 //
 // dW: its epilogue's partial sums grow with the number of tiles, so tiles stay 256 x 256 and an output with
-// fewer than one per CU splits the tokens instead, as far as every block keeps six K-tiles (its epilogue
+// fewer than one per CU splits the tokens instead, as far as every block keeps four K-tiles (its epilogue
 // costs about ten): 1024 x 4096, T = 4096 144 -> 62 us in four splits.
 GemmPlan gemm_plan(GemmVariant v, bool act, bool grouped, bool al16, int64_t M, int64_t N, int64_t K) {
   GemmPlan g;
   auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
   if (v == kDw) {
-    const int64_t nk = (K + 63) / 64, most = std::min<int64_t>(256 / std::max<int64_t>(tiles(256, 256), 1), nk / 6);
+    const int64_t nk = (K + 63) / 64, most = std::min<int64_t>(256 / std::max<int64_t>(tiles(256, 256), 1), nk / 4);
     if (most > 1) {
       g.kts = (nk + most - 1) / most;
       g.split = int((nk + g.kts - 1) / g.kts);
