@@ -104,7 +104,8 @@ hipError_t launch_reduce2(const Reduce2Args& ra0, hipStream_t st) {
 //
 // dW: its epilogue's partial sums grow with the number of tiles, so tiles stay 256 x 256 and an output with
 // fewer than one per CU splits the tokens instead, as far as every block keeps four K-tiles (its epilogue
-// costs about ten): 1024 x 4096, T = 4096 144 -> 62 us in four splits.
+// costs about ten): 1024 x 4096, T = 4096 144 -> 62 us in four splits; 1003 x 2730, T = 1357 61 -> 51 in five
+// splits of four or five K-tiles, against three splits of eight.
 GemmPlan gemm_plan(GemmVariant v, bool act, bool grouped, bool al16, int64_t M, int64_t N, int64_t K) {
   GemmPlan g;
   auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };

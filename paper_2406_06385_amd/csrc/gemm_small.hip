@@ -19,7 +19,7 @@
 // Measured (HIP-graph replays, weights of several layers in turn; 256 x 256 tiles
 // -> this kernel), bf16 tokens: 4096 x 4096, T = 1 84 -> 7.2 us, T = 128 84 -> 26;
 // 14336 x 4096, T = 1 85 -> 18, T = 64 86 -> 39; int8 tokens with their
-// quantisation: 14336 x 4096, T = 24 104 -> 18, 4096 x 14336, T = 128 331 -> 45.
+// quantisation: 14336 x 4096, T = 24 104 -> 16, 4096 x 14336, T = 128 331 -> 45.
 #include "gemm_impl.h"
 
 namespace lrqat {
