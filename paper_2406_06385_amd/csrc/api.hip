@@ -83,7 +83,7 @@ struct Dims {
 };
 
 struct Workspace {
-  size_t q = 0, mask = 0, n = 0, xh = 0, sx = 0, nsum = 0, dA_part = 0, dB_part = 0, ds_part = 0, dW = 0, total = 0;
+  size_t q = 0, mask = 0, n = 0, xh = 0, sx = 0, nsum = 0, dA_part = 0, dB_part = 0, ds_part = 0, tile_part = 0, dW = 0, total = 0;
   GemmPlan dw;
 };
 
@@ -157,10 +157,11 @@ Workspace layout_plan(const Dims& d, int64_t T, Pass pass, const GemmPlan& dw) {
   }
   if (pass == kBackward) {
     if (d.bf16) {
-      w.ds_part = take(size_t(dw.split * d.m * (d.kpad / 32) * 4));
+      w.ds_part = take(size_t(d.m * (d.kpad / 32) * 4));
       const int64_t ntn = (d.k + dw.tn - 1) / dw.tn, ntm = (d.m + dw.tm - 1) / dw.tm;
-      w.dA_part = take(size_t(dw.split * ntn * d.m * d.r * 4));
-      w.dB_part = take(size_t(dw.split * ntm * d.r * d.k * 4));
+      w.dA_part = take(size_t(ntn * d.m * d.r * 4));
+      w.dB_part = take(size_t(ntm * d.r * d.k * 4));
+      if (dw.split > 1) w.tile_part = take(size_t(dw.split * ntm * ntn * dw.tm * dw.tn * 4));
     } else {
       w.dW = take(size_t(d.m * d.k * 4));
     }
@@ -416,12 +417,13 @@ lrqat_status backward_impl(const lrqat_layer* layer, int64_t tokens, const void*
   p.Am = A; p.Bm = B; p.r = int(d.r);
   p.dA_part = dA_part; p.dB_part = dB_part;
   p.plan = w.dw;
+  p.tile_part = reinterpret_cast<float*>(base + w.tile_part);
   if (ds) {
     p.qd = q; p.ldqd = ga.ldq; p.qd8 = d.q8w;
     p.ds_part = ds_part; p.ldds = d.kpad / 32;
   }
   LRQAT_TRY(hip_status(timed("gemm_dw", st, [&] { return launch_gemm(kDw, false, d.g != 0, 0, p, st); }), "gemm_dw"));
-  const int64_t ntn = w.dw.split * ((d.k + w.dw.tn - 1) / w.dw.tn), ntm = w.dw.split * ((d.m + w.dw.tm - 1) / w.dw.tm);
+  const int64_t ntn = (d.k + w.dw.tn - 1) / w.dw.tn, ntm = (d.m + w.dw.tm - 1) / w.dw.tm;
   Reduce2Args ra{};
   ra.part[0] = dA_part; ra.nparts[0] = ntn; ra.n[0] = d.m * d.r; ra.out[0] = dA;
   ra.part[1] = dB_part; ra.nparts[1] = ntm; ra.n[1] = d.r * d.k; ra.out[1] = dB;
@@ -432,7 +434,7 @@ lrqat_status backward_impl(const lrqat_layer* layer, int64_t tokens, const void*
     ra.ds = ds; ra.ds_part = ds_part;
     ra.m = d.m; ra.ldds = d.kpad / 32; ra.nchunks = (d.k + 31) / 32;
     ra.cpg = d.g ? d.g / 32 : ra.nchunks;
-    ra.ngroups = d.ngroups; ra.nsplit = w.dw.split;
+    ra.ngroups = d.ngroups;
   }
   LRQAT_TRY(hip_status(timed("reduce", st, [&] { return launch_reduce2(ra, st); }), "reduce"));
   return LRQAT_OK;

@@ -17,7 +17,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ part, 
   out[idx] = (accumulate ? out[idx] : 0.f) + c * s;
 }
 
-// ds[row][grp] = (accumulate ? ds : 0) + the partials of the group's 32-column chunks over all splits.
+// ds[row][grp] = (accumulate ? ds : 0) + the partials of the group's 32-column chunks.
 // 2^lg consecutive lanes share a (row, group): each takes every 2^lg-th chunk (coalesced), and their sums
 // meet in a fixed tree, so the result is deterministic.  (One thread per row, whose loads are a row apart,
 // took 47 us for 4096 rows of 344 chunks.)
@@ -30,10 +30,8 @@ __device__ __forceinline__ void reduce_ds(const Reduce2Args& ra, int64_t t) {
   if (in) {
     const int64_t row = int64_t(I(idx) / I(ra.ngroups)), grp = idx - row * ra.ngroups;
     const int64_t c0 = grp * ra.cpg, c1 = min(ra.nchunks, c0 + ra.cpg);
-    for (int q = 0; q < ra.nsplit; ++q) {
-      const float* src = ra.ds_part + (q * ra.m + row) * ra.ldds;
-      for (int64_t c = c0 + l; c < c1; c += int64_t(1) << ra.lg) s += src[c];
-    }
+    const float* src = ra.ds_part + row * ra.ldds;
+    for (int64_t c = c0 + l; c < c1; c += int64_t(1) << ra.lg) s += src[c];
   }
   for (int off = (1 << ra.lg) >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off);
   if (in && l == 0) ra.ds[idx] = (ra.accumulate ? ra.ds[idx] : 0.f) + s;
@@ -102,18 +100,23 @@ hipError_t launch_reduce2(const Reduce2Args& ra0, hipStream_t st) {
 // 640 tokens through 11008 x 4096 (129 tiles of 256 x 256) 98 -> 70 us, of 4096 tokens through 1024 x 4096 94 ->
 // 49; dX of 2048 tokens through 14336 x 4096 (128 tiles) 339 -> 254.
 //
-// dW: its epilogue's partial sums grow with the number of tiles, so tiles stay 256 x 256 and an output with
-// fewer than one per CU splits the tokens instead, as far as every block keeps four K-tiles (its epilogue
-// costs about ten): 1024 x 4096, T = 4096 144 -> 62 us in four splits; 1003 x 2730, T = 1357 61 -> 51 in five
-// splits of four or five K-tiles, against three splits of eight.
+// dW: its epilogue and its partial sums grow with the number of tiles, so an output of more than 128 tiles of
+// 256 x 256 keeps them.  A smaller one, which would leave half the chip without a tile, takes 128 x 128 tiles if one
+// per CU covers it, else 256 x 128 (T = 4096: 1024 x 4096, 256 small tiles, 146 -> 70 us; 2048 x 2500, 153 -> 96 in
+// 256 x 128, 105 in 128 x 128).  Where even 128 x 128 tiles are at most half the CUs, the blocks of a tile share its
+// tokens, and a second launch adds their float32 sums before anything is rounded: at least eight K-tiles for
+// each, which is what that launch costs (1024 x 1024: T = 2048 42 -> 30 us in four ranges, T = 512 21 -> 23 in
+// two), and 16 ranges at most, which one block adds in turn (256 x 256, T = 8192: 124 us, 36 in 16, 42 in 32).
 GemmPlan gemm_plan(GemmVariant v, bool act, bool grouped, bool al16, int64_t M, int64_t N, int64_t K) {
   GemmPlan g;
   auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
   if (v == kDw) {
-    const int64_t nk = (K + 63) / 64, most = std::min<int64_t>(256 / std::max<int64_t>(tiles(256, 256), 1), nk / 4);
-    if (most > 1) {
-      g.kts = (nk + most - 1) / most;
-      g.split = int((nk + g.kts - 1) / g.kts);
+    const int64_t n22 = tiles(128, 128);
+    if (n22 <= 256) {
+      g.tm = g.tn = 128;
+      g.split = int(std::max<int64_t>(1, std::min<int64_t>({256 / n22, (K + 63) / 64 / 8, 16})));
+    } else if (tiles(256, 256) <= 128) {
+      g.tn = 128;
     }
     return g;
   }

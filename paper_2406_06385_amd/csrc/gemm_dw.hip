@@ -3,6 +3,6 @@
 
 namespace lrqat {
 
-hipError_t launch_dw_pc(const GemmArgs& p, hipStream_t st) { return launch_variant<kDw, kActNone, false, 0>(p, st); }
+hipError_t launch_dw_pc(const GemmArgs& p, hipStream_t st) { return launch_dw<false>(p, st); }
 
 }  // namespace lrqat

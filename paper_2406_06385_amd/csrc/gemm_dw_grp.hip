@@ -3,6 +3,6 @@
 
 namespace lrqat {
 
-hipError_t launch_dw_grp(const GemmArgs& p, hipStream_t st) { return launch_variant<kDw, kActNone, true, 0>(p, st); }
+hipError_t launch_dw_grp(const GemmArgs& p, hipStream_t st) { return launch_dw<true>(p, st); }
 
 }  // namespace lrqat

@@ -12,8 +12,8 @@
 // s applied in the epilogue (forward, per channel) or folded into the tile
 // (dX, and the forward with group-wise scales).
 //
-// Block tile 256 x 256 x 64 (128 x 128 x 64 where that fills the chip better),
-// four waves in a 2 x 2 arrangement, each wave a quarter of it as 4 x 4 (2 x 2)
+// Block tile 256 x 256 x 64, or 256 x 128, 128 x 256, 128 x 128 where that fills the
+// chip better; four waves in a 2 x 2 arrangement, each wave a quarter of it in
 // MFMA 32x32x16 blocks.  Two LDS stages of bfloat16 tiles; the next K-tile is
 // fetched into registers while the current one feeds the MFMAs.  The forward
 // and dX output tiles leave through LDS as whole row segments.
@@ -330,7 +330,9 @@ __device__ __forceinline__ void store_q_x16_one(uint16_t* tile, const RegsQ16<NQ
 // covers RW consecutive tile rows RW (t/8) .. (one vector per K-line; RW = 8
 // for a 256-row tile, 4 for 128 rows of q) of the 8 K-lines 8 (t%8) .. +7 and
 // transposes them in registers into RW chunks; the 8 lanes of a K-group fill
-// one 128-byte row segment of LDS.
+// one 128-byte row segment of LDS.  128 rows of bfloat16 keep the 16-byte
+// vectors (8 tile rows 8 (t/16) ..) and take 4 K-lines 4 (t%16) .. +3 each, in
+// chunks of 8 bytes.
 // Columns past a tensor's width only feed output rows/columns that the
 // epilogue discards; K-lines past the end read as zeros.
 
@@ -439,40 +441,41 @@ __device__ __forceinline__ void store_q_ks8_one(uint16_t* tile, const RegsQKs8& 
 // bfloat16 (dW A = dY, dW B = X): a 16-byte vector per K-line; with an odd
 // ld the odd K-lines start in the middle of a dword (an extra dword each).
 // kAlOdd: at least one of the two operands has an odd ld (`odd` is uniform).
-template <int AL>
+// KL: K-lines per thread (8 for a 256-row tile, 4 for 128 rows).
+template <int AL, int KL>
 struct RegsKs {
-  u32x4 v[8];
-  uint32_t x[AL == kAlOdd ? 4 : 1];
+  u32x4 v[KL];
+  uint32_t x[AL == kAlOdd ? KL / 2 : 1];
   bool odd;
 };
 
-template <int AL>
-__device__ __forceinline__ void load_ks_bf16(RegsKs<AL>& R, const uint16_t* __restrict__ src, int64_t ld,
+template <int AL, int KL>
+__device__ __forceinline__ void load_ks_bf16(RegsKs<AL, KL>& R, const uint16_t* __restrict__ src, int64_t ld,
                                              int64_t c0, int64_t k0, int64_t K, int w0, int w1) {
   const int t = threadIdx.x;
-  const int kg = t & 7, a = t >> 3;
+  const int kg = t & (64 / KL - 1), a = t / (64 / KL);
   const auto r = rsrc4(src + k0 * ld + c0, (K - k0) * ld * 2 - c0 * 2);
-  const uint32_t base = uint32_t((8 * kg * ld + 8 * a) * 2), step = uint32_t(ld * 2);
+  const uint32_t base = uint32_t((KL * kg * ld + 8 * a) * 2), step = uint32_t(ld * 2);
   R.odd = AL == kAlOdd && (ld & 1);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
+  for (int e = 0; e < KL; ++e) {
     if (e < w0 || e >= w1) continue;
     // a K-line past the end must read zeros: with an odd count of elements the first one's leading dword
     // holds the last element and two bytes beyond the tensor
-    const uint32_t off = AL == kAlOdd ? (k0 + 8 * kg + e < K ? (base + e * step) & ~3u : 0xFFFFFF00u) : base + e * step;
+    const uint32_t off = AL == kAlOdd ? (k0 + KL * kg + e < K ? (base + e * step) & ~3u : 0xFFFFFF00u) : base + e * step;
     R.v[e] = ld128(r, off);
     if constexpr (AL == kAlOdd)
       if (e & 1) R.x[e >> 1] = ld32(r, off + 16);
   }
 }
 
-template <int AL>
-__device__ __forceinline__ void store_ks_bf16_one(uint16_t* tile, const RegsKs<AL>& R, int c) {
+template <int AL, int KL>
+__device__ __forceinline__ void store_ks_bf16_one(uint16_t* tile, const RegsKs<AL, KL>& R, int c) {
   const int t = threadIdx.x;
-  const int kg = t & 7, a = t >> 3;
-  u32x4 o;
+  const int kg = t & (64 / KL - 1), a = t / (64 / KL);
+  typename std::conditional<KL == 8, u32x4, u32x2>::type o;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < KL / 2; ++q) {
     const uint32_t x = R.v[2 * q][c >> 1];
     if constexpr (AL == kAlOdd) {
       // element c of the odd line is half word c (odd ld: c + 1) of its loaded dwords
@@ -484,7 +487,7 @@ __device__ __forceinline__ void store_ks_bf16_one(uint16_t* tile, const RegsKs<A
       o[q] = (c & 1) ? perm_hi16(x, y) : perm_lo16(x, y);
     }
   }
-  *reinterpret_cast<u32x4*>(tile + tile_off(8 * a + c, kg)) = o;
+  *reinterpret_cast<decltype(o)*>(tile + tile_off(8 * a + c, KL * kg >> 3) + (KL * kg & 7)) = o;
 }
 
 // ------------------------------------------------------------------ the kernel
@@ -494,15 +497,15 @@ struct Loader;
 
 // load(.., w0, w1): global loads w0 .. w1 - 1 of the NLD of a tile, the A operand's first (the scales and
 // zero offsets of the B operand ride on its first one).
-// store_one(w): LDS store w of the tile held in registers, w = 0 .. 2 MI - 1 for
-// the A operand and 2 MI .. 2 (MI + NJ) - 1 for the B operand.
+// store_one(w): LDS store w of the NST of the tile held in registers, the A operand's first (2 MI and 2 NJ; dW
+// 8 and 8).
 template <int ACT, bool GRP, int AL, int OPT, int MI, int NJ>
 struct Loader<kFwd, ACT, GRP, AL, OPT, MI, NJ> {
   static constexpr bool ZP = (OPT & kOptZ) != 0, Q8 = (OPT & kOptQ8) != 0;
   typename std::conditional<ACT == kActWide, RegsKc8<2 * MI>, RegsKc<ACT == kActI8 ? kAl16 : AL, 2 * MI>>::type ra;
   typename std::conditional<ACT == kActI8, typename std::conditional<Q8, RegsKc<kAl16, 2 * NJ>, RegsQ16<NJ>>::type,
                             typename std::conditional<Q8, RegsQKc8<2 * NJ>, RegsQKc<NJ / 2>>::type>::type rb;
-  static constexpr int NA = 2 * MI, NB = Q8 ? 2 * NJ : ACT == kActI8 ? NJ : NJ / 2, NLD = NA + NB;
+  static constexpr int NA = 2 * MI, NB = Q8 ? 2 * NJ : ACT == kActI8 ? NJ : NJ / 2, NLD = NA + NB, NST = 2 * (MI + NJ);
   __device__ __forceinline__ void load(const GemmArgs& p, int64_t m0, int64_t n0, int64_t k0, int w0, int w1) {
     if constexpr (ACT == kActI8) {
       // rows of bytes as rows of half as many 16-bit values
@@ -536,7 +539,7 @@ struct Loader<kDx, ACT, GRP, AL, OPT, MI, NJ> {
   static constexpr int RW = 2 * NJ;
   RegsKc<AL, 2 * MI> ra;
   typename std::conditional<Q8, RegsQKs8, RegsQKs>::type rb;
-  static constexpr int NA = 2 * MI, NLD = NA + 8;
+  static constexpr int NA = 2 * MI, NLD = NA + 8, NST = 2 * (MI + NJ);
   __device__ __forceinline__ void load(const GemmArgs& p, int64_t m0, int64_t n0, int64_t k0, int w0, int w1) {
     load_kc_bf16<AL, 2 * MI>(ra, static_cast<const uint16_t*>(p.a), p.lda, m0, p.M, k0, p.K, w0, w1);
     if constexpr (Q8) load_q_ks8<GRP, ZP, RW>(rb, p, n0, k0, w0 - NA, w1 - NA);
@@ -555,16 +558,16 @@ struct Loader<kDx, ACT, GRP, AL, OPT, MI, NJ> {
 template <int ACT, bool GRP, int AL, int OPT, int MI, int NJ>
 struct Loader<kDw, ACT, GRP, AL, OPT, MI, NJ> {
   static_assert(ACT == kActNone, "the dW GEMM reads bfloat16 operands (W4A8: X_hat)");
-  static_assert(MI == 4 && NJ == 4, "256 x 256 tiles only");
-  RegsKs<AL> ra, rb;
-  static constexpr int NLD = 16;
+  static constexpr int KA = 2 * MI, KB = 2 * NJ, NLD = KA + KB, NST = 16;
+  RegsKs<AL, KA> ra;
+  RegsKs<AL, KB> rb;
   __device__ __forceinline__ void load(const GemmArgs& p, int64_t m0, int64_t n0, int64_t k0, int w0, int w1) {
-    load_ks_bf16<AL>(ra, static_cast<const uint16_t*>(p.a), p.lda, m0, k0, p.K, w0, w1);
-    load_ks_bf16<AL>(rb, static_cast<const uint16_t*>(p.b), p.ldb, n0, k0, p.K, w0 - 8, w1 - 8);
+    load_ks_bf16<AL, KA>(ra, static_cast<const uint16_t*>(p.a), p.lda, m0, k0, p.K, w0, w1);
+    load_ks_bf16<AL, KB>(rb, static_cast<const uint16_t*>(p.b), p.ldb, n0, k0, p.K, w0 - KA, w1 - KA);
   }
   __device__ __forceinline__ void store_one(uint16_t* As, uint16_t* Bs, int w) {
-    if (w < 2 * MI) store_ks_bf16_one(As, ra, w);
-    else store_ks_bf16_one(Bs, rb, w - 2 * MI);
+    if (w < 8) store_ks_bf16_one(As, ra, w);
+    else store_ks_bf16_one(Bs, rb, w - 8);
   }
 };
 
@@ -666,6 +669,12 @@ __device__ __forceinline__ void tile_of(int64_t b, int64_t ntm, int64_t ntn, int
   tn = off / gm;
 }
 
+// Element n of a lane's accumulators in a tile's buffer of a split dW: 16 bytes a lane, 1 KiB a wave.
+template <int MI, int NJ>
+__device__ __forceinline__ f32x4* part_at(float* tiles, int64_t tile, int wave, int lane, int n) {
+  return reinterpret_cast<f32x4*>(tiles) + ((tile * 4 + wave) * (MI * NJ * 4) + n) * 64 + lane;
+}
+
 // A block's tile is 64 MI x 64 NJ.  The 256 x 256 tile (one wave per SIMD, 256
 // accumulator registers a wave) reads the fewest LDS bytes per MFMA; the 128 x
 // 128 tile (two blocks a CU) quarters the unit of work for outputs that would
@@ -680,7 +689,8 @@ void k_gemm(GemmArgs p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t ntm = (p.M + BM - 1) / BM, ntn = (p.N + BN - 1) / BN;
   int64_t tm, tn;
-  const int sp = V == kDw ? int(blockIdx.x / uint32_t(ntm * ntn)) : 0;  // dW: split of the tokens
+  constexpr bool kJoin = V == kDw && (OPT & kOptJoin) != 0, kSplit = V == kDw && MI == 2 && NJ == 2 && !kJoin;
+  const int sp = kSplit ? int(blockIdx.x / uint32_t(ntm * ntn)) : 0;  // token range of the tile (plan.split of them)
   tile_of(int64_t(blockIdx.x) - int64_t(sp) * ntm * ntn, ntm, ntn, tm, tn);
   const int64_t m0 = tm * BM, n0 = tn * BN;
   const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
@@ -693,84 +703,102 @@ void k_gemm(GemmArgs p) {
       #pragma unroll
       for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
-  // Software pipeline over K-tiles.  While the MFMAs consume LDS stage kt%2,
-  // the registers holding tile kt+1 are written to the other stage (spread over
-  // k-steps 0..2) and the tile kt+2 is fetched into a second register set from
-  // k-step kLoadStep on.  The one barrier per tile sits before k-step 3, whose
-  // fragments are already in registers, so the first fragments of tile kt+1
-  // are read right after it and their latency hides behind k-step 3's MFMAs.
-  // Loads past the last tile read zeros or unused data and are never
-  // consumed, so the body has no branches.
-  using Ld = Loader<V, ACT, GRP, AL, OPT, MI, NJ>;
-  using S = Sched<V>;
-  constexpr int NST = 2 * (MI + NJ);  // LDS stores of a tile per thread
-  // the block's K-tiles: nk of them from kb on
-  const int nk_all = int((p.K + BK - 1) / BK);
-  const int kts = V == kDw && p.plan.split > 1 ? int(p.plan.kts) : nk_all, kt_first = sp * kts;
-  const int nk = min(kts, nk_all - kt_first);
-  const int64_t kb = int64_t(kt_first) * BK;
-  u32x4 fa[2][MI], fb[2][NJ];
-  auto read = [&](u32x4 (&a)[MI], u32x4 (&b)[NJ], const uint16_t* As, const uint16_t* Bs, int s) {
-    const int ch = 2 * s + (lane >> 5);
+  if constexpr (kJoin) {
+    // the token ranges' sums, added in float32 and in order before anything is rounded
+    for (int q = 0; q < p.plan.split; ++q)
 #pragma unroll
-    for (int i = 0; i < MI; ++i) a[i] = *reinterpret_cast<const u32x4*>(As + tile_off(wm + 32 * i + (lane & 31), ch));
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) b[j] = *reinterpret_cast<const u32x4*>(Bs + tile_off(wn + 32 * j + (lane & 31), ch));
-  };
-  auto mfmas = [&](const u32x4 (&a)[MI], const u32x4 (&b)[NJ]) {
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 v = *part_at<MI, NJ>(p.tile_part, (q * ntm + tm) * ntn + tn, wave, lane, (i * NJ + j) * 4 + g);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        // D = B-tile x A-tile^T: a lane's accumulator holds 4 consecutive output
-        // columns of one output row (8-byte stores; dW: 4 columns of one weight row)
-        acc[i][j] = ACT == kActI8 ? mfma32_i8(b[j], a[i], acc[i][j]) : mfma32(b[j], a[i], acc[i][j]);
-  };
-  // store n of a tile in order: the operands alternate
-  auto order = [](int n) { return MI == NJ ? (n & 1) * 2 * MI + (n >> 1) : n; };
-  Ld L0, L1;
-  L0.load(p, m0, n0, kb, 0, Ld::NLD);
-  L1.load(p, m0, n0, kb + BK, 0, Ld::NLD);
+            for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] += v[e];
+          }
+  } else {
+    // Software pipeline over K-tiles.  While the MFMAs consume LDS stage kt%2,
+    // the registers holding tile kt+1 are written to the other stage (spread over
+    // k-steps 0..2) and the tile kt+2 is fetched into a second register set from
+    // k-step kLoadStep on.  The one barrier per tile sits before k-step 3, whose
+    // fragments are already in registers, so the first fragments of tile kt+1
+    // are read right after it and their latency hides behind k-step 3's MFMAs.
+    // Loads past the last tile read zeros or unused data and are never
+    // consumed, so the body has no branches.
+    using Ld = Loader<V, ACT, GRP, AL, OPT, MI, NJ>;
+    using S = Sched<V>;
+    constexpr int NST = Ld::NST;  // LDS stores of a tile per thread
+    // the block's K-tiles: nk of them from kb on
+    int nk = int((p.K + BK - 1) / BK);
+    int64_t kb = 0;
+    if constexpr (kSplit) {
+      const int first = int(int64_t(nk) * sp / p.plan.split);
+      nk = int(int64_t(nk) * (sp + 1) / p.plan.split) - first;
+      kb = int64_t(first) * BK;
+    }
+    u32x4 fa[2][MI], fb[2][NJ];
+    auto read = [&](u32x4 (&a)[MI], u32x4 (&b)[NJ], const uint16_t* As, const uint16_t* Bs, int s) {
+      const int ch = 2 * s + (lane >> 5);
 #pragma unroll
-  for (int w = 0; w < NST; ++w) L0.store_one(lds, lds + 2 * TA, w);
-  __syncthreads();
-  read(fa[0], fb[0], lds, lds + 2 * TA, 0);
-  auto step = [&](int kt, Ld& Lnext, Ld& Lfree) {
-    const uint16_t* As = lds + (kt & 1) * TA;
-    const uint16_t* Bs = lds + 2 * TA + (kt & 1) * TB;
-    uint16_t* Asn = lds + ((kt + 1) & 1) * TA;
-    uint16_t* Bsn = lds + 2 * TA + ((kt + 1) & 1) * TB;
-    auto kstep = [&](auto sc) {
-      constexpr int s = decltype(sc)::value;
-      constexpr int nls = S::kLoadStep1 - S::kLoadStep0 + 1;
-      constexpr int l0 = s < S::kLoadStep0 ? 0 : s > S::kLoadStep1 ? Ld::NLD : (s - S::kLoadStep0) * Ld::NLD / nls;
-      constexpr int l1 = s < S::kLoadStep0 ? 0 : s >= S::kLoadStep1 ? Ld::NLD : (s + 1 - S::kLoadStep0) * Ld::NLD / nls;
-      constexpr int w0 = s == 0 ? 0 : s == 1 ? (3 * NST + 7) / 8 : (11 * NST + 15) / 16;
-      constexpr int w1 = s == 0 ? (3 * NST + 7) / 8 : s == 1 ? (11 * NST + 15) / 16 : NST;
-      if constexpr (l1 > l0) Lfree.load(p, m0, n0, kb + int64_t(kt + 2) * BK, l0, l1);
-      read(fa[(s + 1) & 1], fb[(s + 1) & 1], As, Bs, s + 1);
-      mfmas(fa[s & 1], fb[s & 1]);
+      for (int i = 0; i < MI; ++i) a[i] = *reinterpret_cast<const u32x4*>(As + tile_off(wm + 32 * i + (lane & 31), ch));
 #pragma unroll
-      for (int w = w0; w < w1; ++w) Lnext.store_one(Asn, Bsn, order(w));
-      interleave_kstep<S, l1 - l0, w1 - w0, MI, NJ>();
+      for (int j = 0; j < NJ; ++j) b[j] = *reinterpret_cast<const u32x4*>(Bs + tile_off(wn + 32 * j + (lane & 31), ch));
+    };
+    auto mfmas = [&](const u32x4 (&a)[MI], const u32x4 (&b)[NJ]) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          // D = B-tile x A-tile^T: a lane's accumulator holds 4 consecutive output
+          // columns of one output row (8-byte stores; dW: 4 columns of one weight row)
+          acc[i][j] = ACT == kActI8 ? mfma32_i8(b[j], a[i], acc[i][j]) : mfma32(b[j], a[i], acc[i][j]);
+    };
+    // store n of a tile in order: the operands alternate
+    auto order = [](int n) { return MI == NJ ? (n & 1) * (NST / 2) + (n >> 1) : n; };
+    Ld L0, L1;
+    L0.load(p, m0, n0, kb, 0, Ld::NLD);
+    L1.load(p, m0, n0, kb + BK, 0, Ld::NLD);
+#pragma unroll
+    for (int w = 0; w < NST; ++w) L0.store_one(lds, lds + 2 * TA, w);
+    __syncthreads();
+    read(fa[0], fb[0], lds, lds + 2 * TA, 0);
+    auto step = [&](int kt, Ld& Lnext, Ld& Lfree) {
+      const uint16_t* As = lds + (kt & 1) * TA;
+      const uint16_t* Bs = lds + 2 * TA + (kt & 1) * TB;
+      uint16_t* Asn = lds + ((kt + 1) & 1) * TA;
+      uint16_t* Bsn = lds + 2 * TA + ((kt + 1) & 1) * TB;
+      auto kstep = [&](auto sc) {
+        constexpr int s = decltype(sc)::value;
+        constexpr int nls = S::kLoadStep1 - S::kLoadStep0 + 1;
+        constexpr int l0 = s < S::kLoadStep0 ? 0 : s > S::kLoadStep1 ? Ld::NLD : (s - S::kLoadStep0) * Ld::NLD / nls;
+        constexpr int l1 = s < S::kLoadStep0 ? 0 : s >= S::kLoadStep1 ? Ld::NLD : (s + 1 - S::kLoadStep0) * Ld::NLD / nls;
+        constexpr int w0 = s == 0 ? 0 : s == 1 ? (3 * NST + 7) / 8 : (11 * NST + 15) / 16;
+        constexpr int w1 = s == 0 ? (3 * NST + 7) / 8 : s == 1 ? (11 * NST + 15) / 16 : NST;
+        if constexpr (l1 > l0) Lfree.load(p, m0, n0, kb + int64_t(kt + 2) * BK, l0, l1);
+        read(fa[(s + 1) & 1], fb[(s + 1) & 1], As, Bs, s + 1);
+        mfmas(fa[s & 1], fb[s & 1]);
+#pragma unroll
+        for (int w = w0; w < w1; ++w) Lnext.store_one(Asn, Bsn, order(w));
+        interleave_kstep<S, l1 - l0, w1 - w0, MI, NJ>();
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      kstep(std::integral_constant<int, 0>{});
+      kstep(std::integral_constant<int, 1>{});
+      kstep(std::integral_constant<int, 2>{});
+      // the last k-step of tile kt (after the barrier) with the first fragment reads of tile kt+1
+      __syncthreads();
+      read(fa[0], fb[0], Asn, Bsn, 0);
+      mfmas(fa[1], fb[1]);
+      interleave_last<MI, NJ>();
       __builtin_amdgcn_sched_barrier(0);
     };
-    kstep(std::integral_constant<int, 0>{});
-    kstep(std::integral_constant<int, 1>{});
-    kstep(std::integral_constant<int, 2>{});
-    // the last k-step of tile kt (after the barrier) with the first fragment reads of tile kt+1
-    __syncthreads();
-    read(fa[0], fb[0], Asn, Bsn, 0);
-    mfmas(fa[1], fb[1]);
-    interleave_last<MI, NJ>();
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  int kt = 0;
-  for (; kt + 1 < nk; kt += 2) {
-    step(kt, L1, L0);
-    step(kt + 1, L0, L1);
+    int kt = 0;
+    for (; kt + 1 < nk; kt += 2) {
+      step(kt, L1, L0);
+      step(kt + 1, L0, L1);
+    }
+    if (kt < nk) step(kt, L1, L0);
   }
-  if (kt < nk) step(kt, L1, L0);
 
   // acc[i][j][4g + e] = C[m0 + wm + 32 i + lane % 32][n0 + wn + 32 j + 8 g + 4 (lane / 32) + e]
   if constexpr (V == kFwd || V == kDx) {
@@ -855,6 +883,18 @@ void k_gemm(GemmArgs p) {
       }
     }
   } else {
+    if constexpr (kSplit)
+      if (p.plan.split > 1) {  // uniform: the sums of the block's tokens, for the launch that joins them
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+              *part_at<MI, NJ>(p.tile_part, (sp * ntm + tm) * ntn + tn, wave, lane, (i * NJ + j) * 4 + g) =
+                  f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+        return;
+      }
     __shared__ float s_tile[BM];                                      // per-channel scales
     __shared__ __attribute__((aligned(16))) uint16_t rt_tile[32 * (BM > BN ? BM : BN)];  // A or B rank block (bf16)
     // ---- dW epilogue: G = s * M * dW staged in LDS as bf16 [row][col], then both
@@ -909,7 +949,7 @@ void k_gemm(GemmArgs p) {
       const auto rq = rsrc(p.qd + (m0 + wm) * p.ldqd, (p.M - m0 - wm) * p.ldqd);  // rows >= M read 0
       // without a zero offset the resource is empty and every z reads 0
       const auto rz = p.z ? rsrc(p.z + (m0 + wm) * p.ngroups, (p.M - m0 - wm) * p.ngroups * 4) : rsrc(p.ds_part, 0);
-      const auto rd = rsrc(p.ds_part + (int64_t(sp) * p.M + m0 + wm) * p.ldds, (p.M - m0 - wm) * p.ldds * 4);
+      const auto rd = rsrc(p.ds_part + (m0 + wm) * p.ldds, (p.M - m0 - wm) * p.ldds * 4);
       const bool q8 = p.qd8 != 0;
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
@@ -1022,9 +1062,9 @@ void k_gemm(GemmArgs p) {
       }
     };
 
-    // dB partial [split][tm][rho][n0 + j] = sum_i A[m0 + i][rho] G[i][j]; dA partial [split][tn][m0 + i][rho] = sum_j G[i][j] B[rho][n0 + j]
-    const auto rdb = rsrc(p.dB_part + (sp * ntm + tm) * r * p.N + n0, (int64_t(r) * p.N - n0) * 4);
-    const auto rda = rsrc(p.dA_part + ((sp * ntn + tn) * p.M + m0) * r, (p.M - m0) * int64_t(r) * 4);
+    // dB partial [tm][rho][n0 + j] = sum_i A[m0 + i][rho] G[i][j]; dA partial [tn][m0 + i][rho] = sum_j G[i][j] B[rho][n0 + j]
+    const auto rdb = rsrc(p.dB_part + tm * r * p.N + n0, (int64_t(r) * p.N - n0) * 4);
+    const auto rda = rsrc(p.dA_part + (tn * p.M + m0) * r, (p.M - m0) * int64_t(r) * 4);
     for (int rb = 0; rb < nrb; ++rb) {
       const int rho = 32 * rb + (lane & 31);
       __syncthreads();  // G staged / previous rank block consumed
@@ -1089,24 +1129,42 @@ hipError_t launch_tile(const GemmArgs& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The instantiation for a plan (all variants share this helper).
+// The instantiation for a plan (the forward and dX variants share this helper).
 template <int V, int ACT, bool GRP, int OPT>
 hipError_t launch_variant(const GemmArgs& p, hipStream_t st) {
   if constexpr (ACT == kActNone) {
-    if (!gemm_al16(GemmVariant(V), false, p.K, p.lda, p.ldb)) {
-      const bool odd = (p.lda & 1) || (V == kDw && (p.ldb & 1));
-      constexpr int B = V == kDw ? 4 : 2;
-      return odd ? launch_tile<V, ACT, GRP, kAlOdd, OPT, B, B>(p, st) : launch_tile<V, ACT, GRP, kAlDword, OPT, B, B>(p, st);
-    }
+    if (!gemm_al16(GemmVariant(V), false, p.K, p.lda, p.ldb))
+      return p.lda & 1 ? launch_tile<V, ACT, GRP, kAlOdd, OPT, 2, 2>(p, st) : launch_tile<V, ACT, GRP, kAlDword, OPT, 2, 2>(p, st);
   }
   if constexpr (V == kDx)
     if (p.plan.tm == 128 && p.plan.tn == 256) return launch_tile<V, ACT, GRP, kAl16, OPT, 2, 4>(p, st);
-  if constexpr (V != kDw && ACT == kActNone)
+  if constexpr (ACT == kActNone)
     if (p.plan.tm == 256 && p.plan.tn == 128) return launch_tile<V, ACT, GRP, kAl16, OPT, 4, 2>(p, st);
-  if constexpr (V != kDw)
-    if (p.plan.tm == 128 && p.plan.tn == 128) return launch_tile<V, ACT, GRP, kAl16, OPT, 2, 2>(p, st);
+  if (p.plan.tm == 128 && p.plan.tn == 128) return launch_tile<V, ACT, GRP, kAl16, OPT, 2, 2>(p, st);
   if (p.plan.tm != 256 || p.plan.tn != 256) return hipErrorInvalidValue;
   return launch_tile<V, ACT, GRP, kAl16, OPT, 4, 4>(p, st);
+}
+
+// dW in tiles of 64 MI x 64 NJ.
+template <bool GRP, int MI, int NJ>
+hipError_t launch_dw_tile(const GemmArgs& p, hipStream_t st) {
+  if (gemm_al16(kDw, false, p.K, p.lda, p.ldb)) return launch_tile<kDw, kActNone, GRP, kAl16, 0, MI, NJ>(p, st);
+  if ((p.lda | p.ldb) & 1) return launch_tile<kDw, kActNone, GRP, kAlOdd, 0, MI, NJ>(p, st);
+  return launch_tile<kDw, kActNone, GRP, kAlDword, 0, MI, NJ>(p, st);
+}
+template <bool GRP>
+hipError_t launch_dw(const GemmArgs& p, hipStream_t st) {
+  const GemmPlan& g = p.plan;
+  if (g.split == 1) {
+    if (g.tm == 256 && g.tn == 256) return launch_dw_tile<GRP, 4, 4>(p, st);
+    if (g.tm == 256 && g.tn == 128) return launch_dw_tile<GRP, 4, 2>(p, st);
+    if (g.tm == 128 && g.tn == 128) return launch_dw_tile<GRP, 2, 2>(p, st);
+  }
+  if (g.tm != 128 || g.tn != 128 || g.split < 1 || !p.tile_part) return hipErrorInvalidValue;
+  const hipError_t e = launch_dw_tile<GRP, 2, 2>(p, st);
+  if (e != hipSuccess) return e;
+  k_gemm<kDw, kActNone, GRP, kAl16, kOptJoin, 2, 2><<<unsigned(((p.M + 127) / 128) * ((p.N + 127) / 128)), 256, 0, st>>>(p);
+  return hipGetLastError();
 }
 
 // Run-time choice of the grouped-scale and zero-offset instantiations of one

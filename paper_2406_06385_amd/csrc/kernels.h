@@ -31,12 +31,11 @@ struct GridArgs {
 // sources and epilogue chosen by the kernel variant.
 enum GemmVariant { kFwd = 0, kDx = 1, kDw = 2 };
 
-// Work split of a GEMM: block tiles of tm x tn outputs (256 or 128 each); for dW `split` blocks per tile,
-// which take kts K-tiles of 64 tokens each.
+// Work split of a GEMM: block tiles of tm x tn outputs (256 or 128 each); for dW in 128 x 128 tiles `split`
+// blocks per tile, each for a range of the tokens.
 struct GemmPlan {
   int tm = 256, tn = 256;
   int split = 1;
-  int64_t kts = 0;
 };
 
 struct GemmArgs {
@@ -57,13 +56,14 @@ struct GemmArgs {
   const float* Am;        // kDw: A [m][r]
   const float* Bm;        // kDw: B [r][k]
   int r;
-  float* dA_part;         // kDw: [split][column tiles][M][r]
-  float* dB_part;         // kDw: [split][row tiles][r][N]
+  float* dA_part;         // kDw: [column tiles][M][r]
+  float* dB_part;         // kDw: [row tiles][r][N]
   const uint8_t* qd;      // kDw with kOptDs: q [M][ldqd] (packed int4, or int8 with kOptQ8)
   int64_t ldqd;
-  float* ds_part;         // kDw, nullable: [split][M][ldds], sums over 32-column chunks of dW (q - z)
+  float* ds_part;         // kDw, nullable: [M][ldds], sums over 32-column chunks of dW (q - z)
   int64_t ldds;
   int qd8;                // kDw with ds_part: qd is int8
+  float* tile_part;       // kDw with plan.split > 1: [split][tiles][tm * tn] sums of the token ranges
   GemmPlan plan;
 };
 
@@ -71,10 +71,11 @@ struct GemmArgs {
 // codes on the int8 MFMA.
 enum : int { kActNone = 0, kActWide = 1, kActI8 = 2 };
 
-// Variant options of the forward and dX GEMMs (bit flags).
+// Variant options of the GEMMs (bit flags).
 enum : int {
   kOptZ = 1,   // zero offset: the weight operand is s (q - z)
-  kOptQ8 = 2   // the integer grid q is int8 (grids of 5..7 bits) instead of packed int4
+  kOptQ8 = 2,  // the integer grid q is int8 (grids of 5..7 bits) instead of packed int4
+  kOptJoin = 4  // dW: the epilogue alone, on the sum of the token ranges
 };
 
 constexpr int kColPad = 256;  // q, mask and code rows are padded to a multiple of this
@@ -128,11 +129,10 @@ struct Reduce2Args {        // side 0: dA, side 1: dB
   int vec[2];               // 16-byte aligned rows and n % 4 == 0
   float c;
   int accumulate;
-  // ds[row][grp] (nullable) = (accumulate ? ds : 0) + the 32-column chunk partials [nsplit][m][ldds] of the group
+  // ds[row][grp] (nullable) = (accumulate ? ds : 0) + the 32-column chunk partials [m][ldds] of the group
   float* ds;
   const float* ds_part;
   int64_t m, ldds, nchunks, cpg, ngroups;  // chunks of a row and of a group
-  int nsplit;
   int lg;                   // set by launch_reduce2
   int64_t nblocks;
 };

@@ -7,6 +7,8 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from oracle import lrqat_oracle as O
+from test_gpu_parity import rel_fro
 from test_gpu_parity_next import Layer, check_layer
 
 pytestmark = pytest.mark.gpu
@@ -81,3 +83,41 @@ def test_bytes_past_a_tensor_stay_out(lr, m, k, T):
 
     c.d_X, c.d_dY = tight(c.d_X), tight(c.d_dY)
     check_layer(lr, c)
+
+
+DW = [
+    # m, k, T, r, bits, fmt, g, asym
+    (2050, 2100, 70, 5, 4, "int_packed2", 0, False),     # 256 x 128 tiles, rows on dwords, one past the tiles in both
+    (2051, 2101, 130, 33, 4, "q8", 0, False),            # the same with odd rows, ranks past one block of 32
+    (2056, 2176, 64, 8, 3, "int_packed2", 128, True),    # the same with groups and offsets, 16-byte rows
+    (129, 257, 1030, 32, 6, "q8", 0, False),             # 128 x 128, two ranges of tokens (8 and 9 K-tiles), odd rows
+    (384, 640, 2050, 20, 4, "int_packed2", 128, False),  # four ranges, a last K-tile of two tokens, groups
+    (130, 130, 8192, 8, 4, "q8", 0, True),               # 16 ranges, offsets, rows on dwords
+]
+
+
+@pytest.mark.parametrize("case", DW, ids=[f"m{s[0]}k{s[1]}T{s[2]}r{s[3]}b{s[4]}g{s[6]}{'z' if s[7] else ''}" for s in DW])
+def test_dw_tiles_and_token_ranges(lr, case):
+    m, k, T, r, bits, fmt, g, asym = case
+    c = Layer(lr, m, k, T, r, float(r), bits, fmt, g, 0, "bf16", asym=asym, seed=600 + m, b_std=0.02,
+              shift=0.01 if asym else 0.0)
+    check_layer(lr, c)
+
+
+@pytest.mark.parametrize("m,k,T,r", [(256, 256, 4096, 32), (500, 701, 1999, 20), (1024, 4096, 1024, 32)])
+def test_cancelling_tokens(lr, m, k, T, r):
+    """Tokens whose parts of dW nearly cancel: all of them meet in float32 before G is rounded, however the
+    tokens are shared out.  dA and dB then carry two bfloat16 roundings a term (G, and B or A), each at most
+    2^-9 of it: below 2 * 2^-9 = 3.9e-3 together, 5e-3 with the rest.
+    The float32 sums, of parts 64 times the result, add 64 * 2^-24 sqrt(T) < 3e-4."""
+    c = Layer(lr, m, k, T, r, float(r), 4, "q8", 0, 0, "bf16", seed=700 + m, b_std=1e-3)
+    h = T // 2
+    c.d_X[h:2 * h] = c.d_X[:h]
+    c.d_dY[h:2 * h] = -(c.d_dY[:h].float() * (1 + 2.0 ** -6)).bfloat16()
+    _, dA, dB = lr.lrqat_backward(c.spec, c.d_X, c.d_phi, c.d_s, c.d_A, c.d_B, c.d_dY, want_dx=False)
+    torch.cuda.synchronize()
+    host = lambda t: t.float().cpu().numpy().astype(np.float64)
+    gr = O.backward(c.L, host(c.d_X), c.phi_ref, c.s_ref, c.A, c.B, host(c.d_dY))
+    for name, got in (("dA", dA), ("dB", dB)):
+        e = rel_fro(got.cpu().numpy(), gr[name])
+        assert e < 5e-3, (name, e)
