@@ -88,7 +88,9 @@ typedef struct {
 } lrqat_layer;
 
 /* Bytes of workspace lrqat_forward / lrqat_backward need for `tokens` rows.
- * Returns 0 for an invalid layer (see lrqat_last_error()). */
+ * The sizes never fall as `tokens` grows: a workspace for the longest batch
+ * serves the shorter ones.  Returns 0 for an invalid layer (see
+ * lrqat_last_error()). */
 size_t lrqat_forward_workspace_size(const lrqat_layer* layer, int64_t tokens);
 size_t lrqat_backward_workspace_size(const lrqat_layer* layer, int64_t tokens);
 

@@ -84,6 +84,7 @@ struct Dims {
 
 struct Workspace {
   size_t q = 0, mask = 0, n = 0, xh = 0, sx = 0, nsum = 0, dA_part = 0, dB_part = 0, ds_part = 0, tile_part = 0, dW = 0, total = 0;
+  size_t size = 0;  // what the size query returns: total, or more
   GemmPlan dw;
 };
 
@@ -166,7 +167,7 @@ Workspace layout_plan(const Dims& d, int64_t T, Pass pass, const GemmPlan& dw) {
       w.dW = take(size_t(d.m * d.k * 4));
     }
   }
-  w.total = off;
+  w.total = w.size = off;
   return w;
 }
 
@@ -174,13 +175,15 @@ constexpr size_t kStaticScratchBytes = size_t(64) << 20;  // the scratch array o
 
 Workspace layout(const Dims& d, int64_t T, Pass pass) {
   if (pass != kBackward || !d.bf16 || T == 0) return layout_plan(d, T, pass, {});
-  const GemmPlan dw = gemm_plan(kDw, false, d.g != 0, true, d.m, d.k, T);
-  const Workspace w = layout_plan(d, T, pass, dw);
-  if (dw.split == 1 || w.total <= kStaticScratchBytes) return w;
-  // A layer that fits the scratch array of lrqat_backward_static only with one set of partial sums takes
-  // one, in both entry points (so that they give the same bits).
-  const Workspace w1 = layout_plan(d, T, pass, {});
-  return w1.total <= kStaticScratchBytes ? w1 : w;
+  const Workspace w = layout_plan(d, T, pass, gemm_plan(kDw, false, d.g != 0, true, d.m, d.k, T));
+  if (w.total <= kStaticScratchBytes) return w;
+  // A layer that fits the scratch array of lrqat_backward_static only with tiles of 256 x 256 takes them, in both
+  // entry points (so that they give the same bits).  Its size is the array's: every shorter batch needs
+  // that much at most, so that the sizes never fall as the tokens grow.
+  Workspace w1 = layout_plan(d, T, pass, {});
+  if (w1.total > kStaticScratchBytes) return w;
+  w1.size = kStaticScratchBytes;
+  return w1;
 }
 
 GridArgs grid_args(const Dims& d, const void* phi0, const float* A, const float* B, uint8_t* q, uint16_t* mask) {
@@ -280,7 +283,7 @@ size_t lrqat_backward_workspace_size(const lrqat_layer* layer, int64_t tokens) {
     fail(LRQAT_EINVAL, "tokens out of range");
     return 0;
   }
-  return layout(d, tokens, kBackward).total;
+  return layout(d, tokens, kBackward).size;
 }
 
 lrqat_status lrqat_init_from_weights(const lrqat_layer* layer, const float* W0, float* s0_out, int32_t* z0_out,

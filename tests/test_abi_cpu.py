@@ -154,6 +154,41 @@ def test_workspace_sizes_grow_with_tokens_and_backward(lib):
         assert (f2 > f1) == (kw.get("act_bits", 0) == 8)
 
 
+MONOTONE = [  # layers whose backward shares tokens, and sizes at which the partial sums pass the static array
+    dict(out_features=1024, in_features=1024, rank=32),
+    dict(out_features=1024, in_features=4096, rank=128),
+    dict(out_features=1024, in_features=4096, rank=32, act_bits=8),
+    dict(out_features=1024, in_features=4096, rank=64, act_bits=8),
+    dict(out_features=1024, in_features=4096, rank=128, act_bits=8),
+    dict(out_features=2048, in_features=4096, rank=256),
+    dict(out_features=300, in_features=520, rank=20, act_bits=8),
+    dict(out_features=4096, in_features=4096, rank=32, act_bits=8),
+    dict(out_features=512, in_features=512, rank=16, act_dtype="fp32"),
+]
+
+
+@pytest.mark.parametrize("kw", MONOTONE, ids=lambda kw: "-".join(str(v) for v in kw.values()))
+def test_workspace_sizes_never_fall_as_tokens_grow(lib, kw):
+    """A workspace sized for the longest batch serves every shorter one, and the static array takes exactly
+    the layers whose size is within its capacity."""
+    L = _layer(**kw)
+    cap = lib.lrqat_backward_static_capacity()
+    for size in (lib.lrqat_forward_workspace_size, lib.lrqat_backward_workspace_size, lib.lrqat_infer_workspace_size):
+        sizes = [size(ctypes.byref(L), T) for T in range(0, 16384, 8)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    if kw.get("act_dtype") == "fp32":
+        return
+    # refused exactly where one set of partial sums for tiles of 256 x 256 is past the array
+    m, k, r = L.out_features, L.in_features, L.rank
+    up = lambda n: -(-n // 256) * 256
+    for T in range(8, 16384, 504):
+        need = up(m * up(k) // 2) + up(m * up(k) // 8) + (up(2 * T * up(k)) if L.act_bits else 0) + up(m * up(k) // 8)
+        need += up(-(-k // 256) * m * r * 4) + up(-(-m // 256) * r * k * 4)
+        assert (lib.lrqat_backward_workspace_size(ctypes.byref(L), T) > cap) == (need > cap)
+        if need > cap:
+            assert _bwd_static(lib, L, T=T) == lrqat.LRQAT_EWORKSPACE
+
+
 def test_status_strings(lib):
     for code, name in enumerate(["LRQAT_OK", "LRQAT_EINVAL", "LRQAT_EUNSUPPORTED", "LRQAT_EWORKSPACE", "LRQAT_EHIP"]):
         assert lib.lrqat_status_string(code).decode() == name
