@@ -175,15 +175,22 @@ constexpr size_t kStaticScratchBytes = size_t(64) << 20;  // the scratch array o
 
 Workspace layout(const Dims& d, int64_t T, Pass pass) {
   if (pass != kBackward || !d.bf16 || T == 0) return layout_plan(d, T, pass, {});
-  const Workspace w = layout_plan(d, T, pass, gemm_plan(kDw, false, d.g != 0, true, d.m, d.k, T));
-  if (w.total <= kStaticScratchBytes) return w;
-  // A layer that fits the scratch array of lrqat_backward_static only with tiles of 256 x 256 takes them, in both
-  // entry points (so that they give the same bits).  Its size is the array's: every shorter batch needs
-  // that much at most, so that the sizes never fall as the tokens grow.
-  Workspace w1 = layout_plan(d, T, pass, {});
-  if (w1.total > kStaticScratchBytes) return w;
-  w1.size = kStaticScratchBytes;
-  return w1;
+  GemmPlan g = gemm_plan(kDw, false, d.g != 0, true, d.m, d.k, T);
+  const Workspace w = layout_plan(d, T, pass, g);
+  if (w.total <= kStaticScratchBytes || layout_plan(d, T, pass, {}).total > kStaticScratchBytes) return w;
+  // A layer that lrqat_backward_static runs with the small partial sums of 256 x 256 tiles takes, in both entry
+  // points (so that they give the same bits), the best plan that fits its array: fewer token ranges first, then
+  // larger tiles.  Its size is the array's: every shorter batch needs that much at most, so that the sizes
+  // never fall as the tokens grow.
+  for (;;) {
+    if (g.split > 1) --g.split;
+    else if (g.tm == 128) g.tm = 256;
+    else g.tn = 256;
+    Workspace c = layout_plan(d, T, pass, g);
+    if (c.total > kStaticScratchBytes) continue;
+    c.size = kStaticScratchBytes;
+    return c;
+  }
 }
 
 GridArgs grid_args(const Dims& d, const void* phi0, const float* A, const float* B, uint8_t* q, uint16_t* mask) {

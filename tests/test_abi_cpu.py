@@ -189,6 +189,26 @@ def test_workspace_sizes_never_fall_as_tokens_grow(lib, kw):
             assert _bwd_static(lib, L, T=T) == lrqat.LRQAT_EWORKSPACE
 
 
+@pytest.mark.parametrize("kw,T,tm,tn,ranges", [
+    (dict(out_features=1024, in_features=4096, rank=128, act_bits=8), 3000, 128, 128, 1),   # fits as it is
+    (dict(out_features=1024, in_features=4096, rank=128, act_bits=8), 4096, 256, 128, 1),
+    (dict(out_features=1024, in_features=4096, rank=128, act_bits=8), 5000, 256, 256, 1),
+    (dict(out_features=1024, in_features=4096, rank=128, act_bits=8), 6144, 128, 128, 1),   # past the array anyway
+    (dict(out_features=1024, in_features=1024, rank=32, act_bits=8), 20000, 128, 128, 4),
+    (dict(out_features=1024, in_features=1024, rank=32, act_bits=8), 25000, 128, 128, 3),
+    (dict(out_features=1024, in_features=1024, rank=32, act_bits=8), 29000, 128, 128, 1),
+    (dict(out_features=1024, in_features=1024, rank=32, act_bits=8), 32000, 128, 128, 4),   # past the array anyway
+])
+def test_backward_takes_the_best_plan_that_fits_the_static_array(lib, kw, T, tm, tn, ranges):
+    """The bytes that the backward pass asks for (in the message of its size check) tell its tiles."""
+    L = _layer(**kw)
+    m, k, r = L.out_features, L.in_features, L.rank
+    need = m * k // 2 + 2 * (m * k // 8) + 2 * T * k + (-(-k // tn) * m + -(-m // tm) * k) * r * 4
+    need += ranges * m * k * 4 if ranges > 1 else 0
+    assert _bwd(lib, L, T=T, ws_bytes=0) == lrqat.LRQAT_EWORKSPACE
+    assert int(re.search(rb"the (\d+) bytes needed", lib.lrqat_last_error()).group(1)) == need
+
+
 def test_status_strings(lib):
     for code, name in enumerate(["LRQAT_OK", "LRQAT_EINVAL", "LRQAT_EUNSUPPORTED", "LRQAT_EWORKSPACE", "LRQAT_EHIP"]):
         assert lib.lrqat_status_string(code).decode() == name
