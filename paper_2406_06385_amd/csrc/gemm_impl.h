@@ -806,48 +806,72 @@ void k_gemm(GemmArgs p) {
     const int64_t col_l = n0 + wn + 4 * (lane >> 5);
     // per-channel forward scales of the lane's columns (packed q without zero offsets entered as q / 16)
     constexpr float kQScale = V == kFwd && !GRP && (OPT & (kOptZ | kOptQ8)) == 0 && ACT != kActI8 ? 16.f : 1.f;
-    f32x4 cs[NJ][4];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int64_t c = col_l + 32 * j + 8 * g;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) cs[j][g][e] = (V == kFwd && !GRP && c + e < p.N) ? p.s[c + e] * kQScale : 1.f;
-      }
     // The tile goes through LDS (bf16 [BM][BN], 16-byte chunks permuted by row
     // as in g_off) and back to memory as whole row segments: a store
     // instruction then covers whole lines instead of 16 bytes of 32 rows, which
     // shortens the burst of output writes that ends the kernel.
     __syncthreads();  // every wave has read its last fragments
     uint16_t* Cs = lds;
+    if constexpr (V == kFwd && !GRP && ACT == kActNone) {
+      // a column block's scales are loaded when it is stored: all of them beside the accumulators spilled 16
+      // registers of the 256 x 256 tile
+      const auto rs = rsrc(p.s + n0, (p.N - n0) * 4);
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int lr = wm + 32 * i + (lane & 31);
-      const float rs = (V == kFwd && ACT != kActNone && m0 + lr < p.M) ? p.sx[m0 + lr] : 1.f;
-      const double sn = (V == kFwd && ACT == kActI8 && (OPT & kOptZ) && m0 + lr < p.M) ? double(p.nsum[m0 + lr]) : 0.0;
+      for (int j = 0; j < NJ; ++j) {
+        u32x4 cs[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) cs[g] = ld128(rs, uint32_t((wn + 32 * j + 8 * g + 4 * (lane >> 5)) * 4));
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+          const int lr = wm + 32 * i + (lane & 31);
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            float val[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = acc[i][j][4 * g + e] * (__uint_as_float(cs[g][e]) * kQScale);
+            *reinterpret_cast<u32x2*>(Cs + g_off<BN>(lr, wn + 32 * j + 8 * g + 4 * (lane >> 5))) =
+                u32x2{pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3])};
+          }
+        }
+      }
+    } else {
+      f32x4 cs[NJ][4];
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          float val[4];
+          const int64_t c = col_l + 32 * j + 8 * g;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float x = acc[i][j][4 * g + e];
-            if constexpr (ACT == kActI8) {
-              // the exact integer sum of n q (packed q entered as 16 q), less z times the sum of n
-              const int v = __float_as_int(x) >> ((OPT & kOptQ8) ? 0 : 4);
-              x = float(v);
-              if constexpr ((OPT & kOptZ) != 0) {
-                const int64_t c = col_l + 32 * j + 8 * g + e;
-                if (c < p.N) x = float(double(v) - double(p.z[c]) * sn);
-              }
-            }
-            val[e] = x * cs[j][g][e] * rs;
-          }
-          *reinterpret_cast<u32x2*>(Cs + g_off<BN>(lr, wn + 32 * j + 8 * g + 4 * (lane >> 5))) =
-              u32x2{pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3])};
+          for (int e = 0; e < 4; ++e) cs[j][g][e] = (V == kFwd && !GRP && c + e < p.N) ? p.s[c + e] * kQScale : 1.f;
         }
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int lr = wm + 32 * i + (lane & 31);
+        const float rs = (V == kFwd && ACT != kActNone && m0 + lr < p.M) ? p.sx[m0 + lr] : 1.f;
+        const double sn = (V == kFwd && ACT == kActI8 && (OPT & kOptZ) && m0 + lr < p.M) ? double(p.nsum[m0 + lr]) : 0.0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            float val[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              float x = acc[i][j][4 * g + e];
+              if constexpr (ACT == kActI8) {
+                // the exact integer sum of n q (packed q entered as 16 q), less z times the sum of n
+                const int v = __float_as_int(x) >> ((OPT & kOptQ8) ? 0 : 4);
+                x = float(v);
+                if constexpr ((OPT & kOptZ) != 0) {
+                  const int64_t c = col_l + 32 * j + 8 * g + e;
+                  if (c < p.N) x = float(double(v) - double(p.z[c]) * sn);
+                }
+              }
+              val[e] = x * cs[j][g][e] * rs;
+            }
+            *reinterpret_cast<u32x2*>(Cs + g_off<BN>(lr, wn + 32 * j + 8 * g + 4 * (lane >> 5))) =
+                u32x2{pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3])};
+          }
+      }
     }
     __syncthreads();
     constexpr int CH = BN / 8, RPP = 256 / CH;  // chunks of a row, rows per pass

@@ -212,3 +212,28 @@ def test_backward_takes_the_best_plan_that_fits_the_static_array(lib, kw, T, tm,
 def test_status_strings(lib):
     for code, name in enumerate(["LRQAT_OK", "LRQAT_EINVAL", "LRQAT_EUNSUPPORTED", "LRQAT_EWORKSPACE", "LRQAT_EHIP"]):
         assert lib.lrqat_status_string(code).decode() == name
+
+
+def test_gemm_kernels_on_aligned_rows_do_not_spill(lib, tmp_path):
+    """The 256 x 256 tiles hold 256 accumulators a lane; a spilled register costs the forward of the 4096 x 4096
+    layer two percent.  Read from the metadata of the code objects in the library."""
+    readelf = "/opt/rocm/llvm/bin/llvm-readelf"
+    if not os.path.exists(readelf):
+        pytest.skip("llvm-readelf not available")
+    blob = open(lrqat.LIB_PATH, "rb").read()
+    starts = [i.start() for i in re.finditer(b"\x7fELF\x02\x01\x01\x40", blob)]  # OSABI: AMDGPU HSA
+    spills = {}
+    for n, at in enumerate(starts):
+        part = tmp_path / f"{n}.elf"
+        part.write_bytes(blob[at:])
+        notes = subprocess.run([readelf, "--notes", str(part)], capture_output=True, text=True).stdout
+        names = re.findall(r"^ +\.name: +(\S+k_gemm\S+)$", notes, re.M)
+        counts = [int(c) for c in re.findall(r"\.vgpr_spill_count: +(\d+)", notes)]
+        if names:
+            assert len(names) == len(counts), part
+            spills.update(zip(names, counts))
+    assert len(spills) > 50
+    # k_gemm<V, ACT, GRP, AL, OPT, MI, NJ> with AL = 1; int8 tokens widened without groups serve k > 65536 only
+    hot = {n: c for n, c in spills.items()
+           if re.search(r"ILi\dELi\dELb\dELi1E", n) and not re.search(r"ILi0ELi1ELb0E", n)}
+    assert hot and not {n: c for n, c in hot.items() if c}
