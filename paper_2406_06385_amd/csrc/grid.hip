@@ -416,6 +416,14 @@ __device__ __forceinline__ bool grid_decide(const GridArgs& a, const PhiRegs& P,
   return need != 0 && row < a.m;
 }
 
+// Makes the LDS writes of a wave's lanes visible to its other lanes (a wave's LDS accesses are performed in order:
+// this keeps the compiler to it and costs no instruction).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // 16-column pieces with an element to settle (row of the block << 4 | piece of its 256-column strip) go to a
 // queue of their wave, and are settled side by side after its last round, over their tentative results: 16
 // lanes each, an element a lane.  (A float64 delta is a memory round trip; decided inside the round loop
@@ -423,6 +431,7 @@ __device__ __forceinline__ bool grid_decide(const GridArgs& a, const PhiRegs& P,
 // 58.5 -> 34.6 us.)  A wave's queue has room for all its pieces.
 template <bool PACKED, bool MASK, bool Q8OUT>
 __device__ __forceinline__ void grid_drain(const GridArgs& a, const uint16_t* queue, const int* nqueue, int64_t row0, int64_t strip0) {
+  wave_sync();
   const int nq = __builtin_amdgcn_readfirstlane(*nqueue);
   if (nq == 0) return;
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the wave's tentative results are written
@@ -543,6 +552,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
   __shared__ uint16_t queue[4][512];  // per wave (nit <= 8), see grid_drain
   __shared__ int nqueue[4];
   if (lane == 0) nqueue[wave] = 0;
+  wave_sync();
   float bss = 0.f, bmx = 0.f;
   if constexpr (COAL) {
     // B[0..31][col0 .. col0 + 63]: 8 loads of 4 rank rows x 256 bytes, staged raw
@@ -791,6 +801,7 @@ __global__ __launch_bounds__(GR_THREADS, MULTI || Q8OUT ? 2 : 3) void k_grid_w(G
   __shared__ uint16_t queue[4][MULTI ? 256 : 1024];  // per wave, see grid_drain
   __shared__ int nqueue[4];
   if (lane == 0) nqueue[wave] = 0;
+  wave_sync();
 
   // round 0's codes and A rows first: they do not depend on the B fragments
   PhiRegs P[4];
