@@ -65,7 +65,10 @@ typedef enum {
 } lrqat_phi_format;
 
 /* Element type of the activations X, Y, dY, dX ("compute data type",
- * Section 4.2).  A, B, s, s0, W0, dA, dB, ds are always float32. */
+ * Section 4.2).  A, B, s, s0, W0, dA, dB, ds are always float32.
+ * LRQAT_FP32: the contractions with X, dY and the weights take a float32 as
+ * three bfloat16 pieces, which hold it exactly from 2^-110 up; smaller values
+ * carry fewer bits (8 at 2^-126), subnormals count as zero. */
 typedef enum { LRQAT_FP32 = 0, LRQAT_BF16 = 1 } lrqat_dtype;
 
 typedef struct {

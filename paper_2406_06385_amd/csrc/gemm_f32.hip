@@ -2,7 +2,7 @@
 // Section 4.2): the same integer grid and clip mask as the bfloat16 path.
 //
 // The three large contractions run on the bfloat16 matrix cores with float32
-// accuracy.  A float32 x is the exact sum of three bfloat16 pieces x = h + m + l
+// accuracy.  A float32 x of at least 2^-110 is the exact sum of three bfloat16 pieces x = h + m + l
 // of 8 significant bits each, and products of bfloat16 values are exact in float32, so
 //   X W_hat^T  = s (.) (Xh + Xm + Xl) q^T            three products: q is exact in bfloat16
 //   dY W_hat   = ((dY s)h + (dY s)m + (dY s)l) q
@@ -10,6 +10,9 @@
 // With group-wise scales or a zero offset W_hat = fl32(s (q - z)) is split too and
 // both others take six products.  The products with an l or m piece have an
 // accumulator of their own, so the main sum sees one addition per 16 terms.
+// The matrix cores take bfloat16 subnormals as zero, so below 2^-110 the pieces l and then m are lost: a sum
+// whose terms are all of that size is off by 2e-6 of itself at 2^-116, 4e-5 at 2^-120, 2e-3 at 2^-126, and
+// float32 subnormals count as zero.
 // The rank-r contractions of G = s M dW (dW is kept in the workspace) use the
 // float32 MFMA: they are bound by reading dW.
 //
@@ -34,11 +37,12 @@ constexpr int F_THREADS = 512;
 __device__ __forceinline__ int plane_off(int row, int chunk) { return row * FK + ((chunk ^ ((row >> 1) & 3)) << 3); }
 
 // Eight floats -> their three bfloat16 pieces: h truncated (a finite x stays finite), m and l
-// rounded.  An infinite x gives m = l = NaN, which reaches the second accumulator only.
+// rounded.  An infinite x gives m = l = NaN, which reaches the second accumulator only.  NaNs are made quiet
+// first: one whose payload lies in the low half alone would be truncated to an infinity.
 __device__ __forceinline__ void split3(const float (&x)[8], u32x4& h, u32x4& m, u32x4& l) {
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
-    const float a = x[2 * p], b = x[2 * p + 1];
+    const float a = __builtin_canonicalizef(x[2 * p]), b = __builtin_canonicalizef(x[2 * p + 1]);
     const float a1 = a - bf16_hi(__float_as_uint(a)), b1 = b - bf16_hi(__float_as_uint(b));
     const uint32_t mm = pack_bf16x2(a1, b1);
     h[p] = perm_hi16(__float_as_uint(a), __float_as_uint(b));
@@ -318,7 +322,6 @@ __global__ __launch_bounds__(64 * F_WAVES) void k_f32_db(F32Args p, float* __res
     for (int e = 0; e < 4; ++e) acc[q][e] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int64_t nst = (p.m + 3) / 4;
   const int64_t grp = p.gsize ? min<int64_t>(col / p.gsize, p.ngroups - 1) : 0;
-#pragma unroll 4
   for (int64_t st = wave; st < nst; st += F_WAVES) {
     const int64_t r0 = 4 * st;  // rows past m lie outside the resources and read 0
     const u32x4 w = ld128(rsrc(p.dW + r0 * p.k + j0, ((p.m - r0) * p.k - j0) * 4), uint32_t((g * p.k + 4 * i16) * 4));

@@ -138,7 +138,7 @@ struct Reduce2Args {        // side 0: dA, side 1: dB
 };
 hipError_t launch_reduce2(const Reduce2Args& ra, hipStream_t st);
 
-// float32 activation path (simple tiled FMA kernels).
+// float32 activation path (split operands on the bf16 matrix cores).
 struct F32Args {
   int64_t T, m, k;
   int r;

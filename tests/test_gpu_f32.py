@@ -84,3 +84,18 @@ def test_infinities_stay_where_they_belong(lr):
     cols = [j for j in range(160) if j != 7]
     assert torch.equal(got[0], base[0]) and torch.equal(got[2][:, cols], base[2][:, cols])
     assert not torch.isfinite(got[2][:, 7]).any()
+
+
+def test_nan_payloads_survive_the_split(lr):
+    """A signalling NaN whose payload lies in the low 16 bits of the float32 (truncated to bfloat16 it would
+    be an infinity) gives NaN wherever it enters a sum, as plain float32 arithmetic does."""
+    c = Layer(lr, 96, 160, 40, 8, 8.0, 4, "q8", 0, 0, "fp32", seed=471)
+    X, dY = c.d_X.clone(), c.d_dY.clone()
+    for t, i, j, bits in ((X, 3, 7, 0x7F800001), (X, 9, 0, -0x7FFFFF), (dY, 5, 11, 0x7F80FFFF)):
+        t.view(torch.int32)[i, j] = bits
+        assert t[i, j].isnan()
+    Y = lr.lrqat_forward(c.spec, X, c.d_phi, c.d_s, c.d_A, c.d_B)
+    assert Y[[3, 9]].isnan().all() and torch.isfinite(Y[[t for t in range(40) if t not in (3, 9)]]).all()
+    dX, dA, dB = lr.lrqat_backward(c.spec, X, c.d_phi, c.d_s, c.d_A, c.d_B, dY)
+    assert dX[5].isnan().all() and torch.isfinite(dX[[t for t in range(40) if t != 5]]).all()
+    assert dB[:, [0, 7]].isnan().all() and dA[11].isnan().all()
