@@ -7,7 +7,6 @@ The functions keep the C names; tensors must be contiguous and on the GPU.
 from __future__ import annotations
 
 import ctypes
-import functools
 import os
 from dataclasses import dataclass
 
@@ -41,8 +40,13 @@ class _AdamWConfig(ctypes.Structure):
                 ("max_grad_norm", ctypes.c_float), ("total_steps", ctypes.c_int64), ("warmup_steps", ctypes.c_int64)]
 
 
+class _StructSlot:
+    # the C struct of a spec lies in a slot, not among the attributes that vars() and copies see
+    __slots__ = ("_struct",)
+
+
 @dataclass(frozen=True)
-class LayerSpec:
+class LayerSpec(_StructSlot):
     """Hyper-parameters of one LR-QAT linear (mirrors the C struct lrqat_layer)."""
     out_features: int
     in_features: int
@@ -58,13 +62,17 @@ class LayerSpec:
         return _Layer(self.out_features, self.in_features, self.rank, self.alpha, self.bits,
                       _FMT[self.phi_format], self.group_size, self.act_bits, _DT[self.act_dtype])
 
-    @functools.cached_property
+    @property
     def _c(self):
         # the fields are frozen, so one struct serves every call (the library only reads it)
-        return self.c_struct()
+        try:
+            return self._struct
+        except AttributeError:
+            object.__setattr__(self, "_struct", self.c_struct())
+            return self._struct
 
     def __getstate__(self):
-        return {k: v for k, v in self.__dict__.items() if k != "_c"}
+        return dict(self.__dict__)
 
     @property
     def torch_dtype(self):

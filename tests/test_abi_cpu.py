@@ -237,3 +237,19 @@ def test_gemm_kernels_on_aligned_rows_do_not_spill(lib, tmp_path):
     hot = {n: c for n, c in spills.items()
            if re.search(r"ILi\dELi\dELb\dELi1E", n) and not re.search(r"ILi0ELi1ELb0E", n)}
     assert hot and not {n: c for n, c in hot.items() if c}
+
+
+def test_layer_spec_keeps_its_own_fields_only():
+    """The C struct that a spec keeps for its calls is no part of its attributes: vars(), copies, pickles and
+    comparisons see the fields alone, before and after a call."""
+    import copy
+    import dataclasses
+    import pickle
+    a = lrqat.LayerSpec(64, 128, 8, 8.0, 4)
+    fields = {f.name: getattr(a, f.name) for f in dataclasses.fields(a)}
+    one = a._c
+    assert vars(a) == fields and lrqat.LayerSpec(**vars(a)) == a
+    for b in (copy.copy(a), copy.deepcopy(a), pickle.loads(pickle.dumps(a)), dataclasses.replace(a, rank=8)):
+        assert b == a and hash(b) == hash(a) and vars(b) == fields
+        assert b._c is not one and bytes(b._c) == bytes(one)
+    assert a._c is one
