@@ -85,29 +85,10 @@ __device__ __forceinline__ int acc_row(int v, int lane) { return 8 * (v >> 2) + 
 // small delta into the stored value.  With n = floor(code / 2^f) and the
 // fraction bits cf = code mod 2^f,
 //     u = n + 1/2 + w,   w = (cf * 2^-f - 1/2) + delta,
-// where the bracket is exact in float32.  For non-integer w the nearest
-// integer is n + ceil(w); an integer w is a tie between n + w and n + w + 1,
-// resolved to the even one.  float32 keeps the sign of w exact (it is 0 only
-// when the bracket cancels delta exactly), so near the usual decision point
-// w = 0 the only error is that of delta itself.  f = 0 is integer Phi0.
-__host__ __device__ __forceinline__ int grid_round(int code, int f, float delta, float* margin = nullptr) {
-  const int n = code >> f;
-  const int cf = code & ((1 << f) - 1);
-  const float w = (float(cf) * __builtin_bit_cast(float, uint32_t(127 - f) << 23) - 0.5f) + delta;
-  const float cw = __builtin_ceilf(w);
-  int ut = n + int(cw);
-  if (cw == w) ut += ut & 1;
-  if (margin) {
-    // distance to the nearest decision point nd, less the rounding error of the
-    // float32 sum there (at most 2^-23 |nd|; the sum is exact near nd = 0)
-    const float nd = __builtin_rintf(w);
-    *margin = __builtin_fabsf(w - nd) - 0x1p-23f * __builtin_fabsf(nd);
-  }
-  return ut;
-}
-
-// The same decision with delta in float64, for elements whose float32 margin
-// does not exceed the error bound of the float32 delta.
+// where the bracket is exact.  For non-integer w the nearest integer is n +
+// ceil(w); an integer w is a tie between n + w and n + w + 1, resolved to the
+// even one.  f = 0 is integer Phi0.  delta is in float64: this settles the
+// elements that the float32 decisions (grid_swar.h) leave open.
 __host__ __device__ __forceinline__ int grid_round_f64(int code, int f, double delta) {
   const int n = code >> f;
   const int cf = code & ((1 << f) - 1);

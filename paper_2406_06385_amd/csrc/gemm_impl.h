@@ -60,14 +60,6 @@ __device__ __forceinline__ uint32_t ld16(__amdgpu_buffer_rsrc_t r, uint32_t off)
 }
 __device__ __forceinline__ float ldf(__amdgpu_buffer_rsrc_t r, uint32_t off) { return __uint_as_float(ld32(r, off)); }
 
-// 8 bfloat16 starting at byte offset `off` with 16-bit loads (rows not 16-byte aligned).
-__device__ __forceinline__ u32x4 ld8_bf16_scalar(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  u32x4 v;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = ld16(r, off + 4 * q) | (ld16(r, off + 4 * q + 2) << 16);
-  return v;
-}
-
 // Zero the elements of an 8-wide bfloat16 chunk at column kk that lie at or past K.
 __device__ __forceinline__ u32x4 mask_tail(u32x4 v, int kk, int K) {
 #pragma unroll

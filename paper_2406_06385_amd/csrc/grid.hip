@@ -299,11 +299,9 @@ __device__ __forceinline__ void grid_clear(const GridArgs& a, GridOut& o, int64_
 // below 1/2 on the whole tile has been copied already).  Returns whether one of
 // the lane's elements lies within the error bound tau of a rounding point: its result is tentative, and the
 // lane's piece is to be queued for grid_drain.
-//  * Q8, |delta| < 1/2: with Phi0 = n + cf 2^-f (n = floor, cf the f fraction bits), u = n + 1/2 + w,
-//    w = (cf 2^-f - 1/2) + delta (one fused multiply-add of exact terms, which keeps the sign of w at any
-//    size of delta), the nearest integer is n + [w > 0], formed byte-parallel;
-//  * else u = Phi0 + delta is rounded in float32 by adding 1.5 2^23: the nearest integer v is then the low
-//    byte (two's complement) of the sum's bits.  Where delta is identically zero (tau < 0: a zero A row;
+//  * Q8, |delta| < 1/2: n + [w > 0] (grid_w), formed byte-parallel;
+//  * else u = Phi0 + delta is rounded in float32 by adding kGridMagic: the nearest integer v is then the low
+//    byte of the sum's bits.  Where delta is identically zero (tau < 0: a zero A row;
 //    zero_delta: zero B columns, the adapters' initial state) this is round-half-even of Phi0 itself.
 // edge (uniform): the tile has columns past k.
 template <bool PACKED, bool MASK, bool B4, bool Q8OUT>
@@ -335,10 +333,7 @@ __device__ __forceinline__ bool grid_decide(const GridArgs& a, const PhiRegs& P,
 #pragma unroll
       for (int v = 0; v < 4; ++v) amx = fmaxf(amx, fabsf(acc[g][v]));
     if (!zero_delta && !__builtin_amdgcn_ballot_w64(!(amx * fabsf(a.c) < 0.5f - tz - 0x1p-20f && tau >= 0.f))) {
-      auto w_of = [&](int g, int v) {
-        const uint32_t fw = P.w[g] & (ones * uint32_t((1 << f) - 1));
-        return __builtin_fmaf(acc[g][v], a.c, __builtin_fmaf(float((fw >> (8 * v)) & 0xffu), sf, -0.5f));
-      };
+      auto w_of = [&](int g, int v) { return grid_w(P.w[g], v, f, acc[g][v], a.c); };
       float wmn = __builtin_inff();
       uint32_t clip = 0;
 #pragma unroll
@@ -362,7 +357,6 @@ __device__ __forceinline__ bool grid_decide(const GridArgs& a, const PhiRegs& P,
     }
   }
   if (!done) {
-    constexpr float kMagic = 12582912.f;
     uint32_t vb[16];
     float dmx = 0.f, vmx = -__builtin_inff(), vmn = __builtin_inff();
     auto u_of = [&](int idx) {
@@ -371,30 +365,27 @@ __device__ __forceinline__ bool grid_decide(const GridArgs& a, const PhiRegs& P,
     };
 #pragma unroll
     for (int idx = 0; idx < 16; ++idx) {
-      const float u = u_of(idx), vm = u + kMagic, v = vm - kMagic;
+      const float u = u_of(idx), vm = u + kGridMagic, v = vm - kGridMagic;
       vb[idx] = __float_as_uint(vm);
       dmx = fmaxf(dmx, fabsf(u - v));
       vmx = fmaxf(vmx, v);
       vmn = fminf(vmn, v);
     }
-    // v is certain unless u lies within the error bound of a half-integer: that of delta and the rounding
-    // of u, below 2^-24 (|v| + 1/2), more than doubled.  Values far off the grid and NaNs (whose norm bounds
-    // are infinite) are left to the exact path too.
-    const float vab = fmaxf(fabsf(vmx), fabsf(vmn));
-    const float thr = vab < 32768.f ? 0.5f - (tz + __builtin_fmaf(0x1p-22f, vab, 0x1p-21f)) : -1.f;
+    // (NaNs, whose norm bounds are infinite, are left to the exact path too)
+    const float thr = grid_certain(tz, fmaxf(fabsf(vmx), fabsf(vmn)));
     const bool sure = zero_delta || tau < 0.f;
     if (__builtin_amdgcn_ballot_w64(!(dmx < thr || sure))) {  // rare
 #pragma unroll
       for (int idx = 0; idx < 16; ++idx) {
         const float u = u_of(idx);
-        need |= uint32_t(!(fabsf(u - (__uint_as_float(vb[idx]) - kMagic)) < thr || sure)) << idx;
+        need |= uint32_t(!(fabsf(u - (__uint_as_float(vb[idx]) - kGridMagic)) < thr || sure)) << idx;
       }
     }
     if (__builtin_amdgcn_ballot_w64(!(vmx <= float(hi) && vmn >= float(lo)))) {
       uint32_t mb = 0;
 #pragma unroll
       for (int idx = 0; idx < 16; ++idx) {
-        const float vm = __uint_as_float(vb[idx]), vc = fminf(fmaxf(vm, kMagic + float(lo)), kMagic + float(hi));
+        const float vm = __uint_as_float(vb[idx]), vc = fminf(fmaxf(vm, kGridMagic + float(lo)), kGridMagic + float(hi));
         if constexpr (MASK) mb |= uint32_t(vm == vc) << idx;
         vb[idx] = __float_as_uint(vc);
       }

@@ -1,4 +1,4 @@
-// Byte-parallel integer-grid decision shared by the grid pass and its host test.
+// The float32 decisions of the grid pass (which its host test runs too).
 #pragma once
 
 #include "common.h"
@@ -22,15 +22,23 @@ __host__ __device__ __forceinline__ uint32_t swar_carry_q8(uint32_t w, uint32_t 
   return qu;
 }
 
-// Byte-parallel grid of four Q8 codes in the regime where delta is smaller than
-// the distance of every non-tie code to its rounding point (|delta| < 2^-f) and
-// its sign is certain: with cf the f fraction bits, round-half-even(n + cf 2^-f
-// + delta) is n plus the carry out of cf + (2^(f-1) - 1) + [delta > 0], since
-// only a tie (cf = 2^(f-1)) depends on delta.  incb holds [delta > 0] per byte.
-__host__ __device__ __forceinline__ uint32_t swar_grid_q8(uint32_t w, uint32_t incb, int f, int b, uint32_t& clip) {
-  const uint32_t ones = 0x01010101u;
-  const uint32_t t = (w & (ones * ((1u << f) - 1))) + ones * ((1u << (f - 1)) - 1) + incb;
-  return swar_carry_q8(w, (t >> f) & ones, f, b, clip);
+// Q8 code v (0..3) of a word, Phi0 = n + cf 2^-f: w of u = Phi0 + delta = n + 1/2 + w, delta = acc c.  The
+// bracket is exact, so the one rounding keeps the sign of w at any size of delta; with |delta| < 1/2 the
+// nearest integer to u is n + [w > 0], certain where |w| exceeds the error bound of delta.
+__host__ __device__ __forceinline__ float grid_w(uint32_t word, int v, int f, float acc, float c) {
+  const float sf = __builtin_bit_cast(float, uint32_t(127 - f) << 23);  // 2^-f
+  const uint32_t fw = word & (0x01010101u * uint32_t((1 << f) - 1));
+  return __builtin_fmaf(acc, c, __builtin_fmaf(float((fw >> (8 * v)) & 0xffu), sf, -0.5f));
+}
+
+// u + kGridMagic is u rounded half to even, the integer v as two's complement in its low bits (|v| < 2^22).
+constexpr float kGridMagic = 12582912.f;  // 1.5 2^23
+
+// v is certain where |u - v| is below this: u no nearer to a half-integer than the error bound tz of delta and
+// the rounding of u, below 2^-24 (|v| + 1/2), more than doubled.  vab: |v|, or the largest of several.
+// Values far off the grid are never certain.
+__host__ __device__ __forceinline__ float grid_certain(float tz, float vab) {
+  return vab < 32768.f ? 0.5f - (tz + __builtin_fmaf(0x1p-22f, vab, 0x1p-21f)) : -1.f;
 }
 
 }  // namespace lrqat

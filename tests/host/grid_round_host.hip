@@ -1,6 +1,5 @@
-// Host driver for the library's grid rounding routines: reads lines
-// "code f delta_bits_hex" (delta as float32 bits) and prints the float32 and
-// the float64 decision.
+// Host driver for the library's exact rounding of Phi0 + delta: reads lines
+// "code f delta_bits_hex" (delta as float64 bits) and prints the decision.
 #include <cstdio>
 #include <cstring>
 
@@ -8,11 +7,11 @@
 
 int main() {
   int code, f;
-  unsigned bits;
-  while (std::scanf("%d %d %x", &code, &f, &bits) == 3) {
-    float delta;
-    std::memcpy(&delta, &bits, 4);
-    std::printf("%d %d\n", lrqat::grid_round(code, f, delta), lrqat::grid_round_f64(code, f, double(delta)));
+  unsigned long long bits;
+  while (std::scanf("%d %d %llx", &code, &f, &bits) == 3) {
+    double delta;
+    std::memcpy(&delta, &bits, 8);
+    std::printf("%d\n", lrqat::grid_round_f64(code, f, delta));
   }
   return 0;
 }

@@ -1,5 +1,6 @@
-"""The library's exact rounding of Phi0 + delta (compiled for the host) against
-exact rational round-half-to-even, including .5 ties and tiny deltas."""
+"""The library's rounding of Phi0 + delta (compiled for the host), exact and as the
+grid pass decides it from a float32 delta with an error bound, against exact
+rational round-half-to-even, including .5 ties and tiny deltas."""
 import math
 import os
 import shutil
@@ -21,18 +22,22 @@ def _rne(x: Fraction) -> int:
     return fl if fl % 2 == 0 else fl + 1
 
 
-@pytest.fixture(scope="module")
-def driver(tmp_path_factory):
+def _compile(tmp_path_factory, name):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
-    exe = str(tmp_path_factory.mktemp("host") / "grid_round_host")
-    src = os.path.join(ROOT, "tests", "host", "grid_round_host.hip")
+    exe = str(tmp_path_factory.mktemp("host") / name)
+    src = os.path.join(ROOT, "tests", "host", name + ".hip")
     cmd = [hipcc, "--offload-arch=gfx950", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2406_06385_amd", "csrc"),
            src, "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     return exe
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    return _compile(tmp_path_factory, "grid_round_host")
 
 
 def _cases():
@@ -61,73 +66,90 @@ def _cases():
 
 def test_grid_round_matches_exact_rne(driver):
     cases = _cases()
-    lines = "".join(f"{c} {f} {struct.unpack('<I', struct.pack('<f', float(d)))[0]:x}\n" for c, f, d in cases)
+    lines = "".join(f"{c} {f} {struct.unpack('<Q', struct.pack('<d', float(d)))[0]:x}\n" for c, f, d in cases)
     r = subprocess.run([driver], input=lines, capture_output=True, text=True)
     assert r.returncode == 0
-    got = [tuple(int(t) for t in line.split()) for line in r.stdout.splitlines()]
+    got = [int(line) for line in r.stdout.splitlines()]
     assert len(got) == len(cases)
-    bad = []
-    for (c, f, d), (g32, g64) in zip(cases, got):
-        want = _rne(Fraction(c, 2 ** f) + Fraction(float(d)))
-        if g32 != want or g64 != want:
-            bad.append((c, f, float(d), g32, g64, want))
+    bad = [(c, f, float(d), g) for (c, f, d), g in zip(cases, got) if g != _rne(Fraction(c, 2 ** f) + Fraction(float(d)))]
     assert not bad, bad[:10]
 
 
 @pytest.fixture(scope="module")
-def swar_driver(tmp_path_factory):
-    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
-    if not os.path.exists(hipcc):
-        pytest.skip("hipcc not available")
-    exe = str(tmp_path_factory.mktemp("host") / "swar_grid_host")
-    src = os.path.join(ROOT, "tests", "host", "swar_grid_host.hip")
-    cmd = [hipcc, "--offload-arch=gfx950", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2406_06385_amd", "csrc"),
-           src, "-o", exe]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr
-    return exe
+def decide_driver(tmp_path_factory):
+    return _compile(tmp_path_factory, "grid_decide_host")
 
 
-def test_byte_parallel_grid_matches_exact_rounding(swar_driver):
-    """Four Q8 codes per word, delta of a known sign and magnitude below 2^-f:
-    each byte's nibble (b <= 4) or whole byte (b >= 5) equals
-    round-half-even(code 2^-f + delta) on the grid,
-    and exactly the codes that would leave the grid are marked for clipping."""
+def _bits(x):
+    return struct.unpack("<I", struct.pack("<f", float(np.float32(x))))[0]
+
+
+def _decisions():
+    """Four codes with their deltas, and the error bound of the deltas."""
     rng = np.random.default_rng(7)
-    cases = []
-    for b in (7, 6, 5, 4, 3, 2):
-        f = 8 - b
-        for code in range(-128, 128):  # every code, in every byte position, both delta signs
-            for pos in range(4):
-                for inc in (0, 1):
-                    others = rng.integers(0, 256, size=4)
-                    others[pos] = code & 0xFF
-                    incs = rng.integers(0, 2, size=4)
-                    incs[pos] = inc
-                    cases.append((others, incs, f, b))
-        for _ in range(2000):
-            cases.append((rng.integers(0, 256, size=4), rng.integers(0, 2, size=4), f, b))
-    lines = []
-    for codes, incs, f, b in cases:
-        w = sum(int(c) << (8 * j) for j, c in enumerate(codes))
-        ib = sum(int(i) << (8 * j) for j, i in enumerate(incs))
-        lines.append(f"{w:x} {ib:x} {f} {b}\n")
-    r = subprocess.run([swar_driver], input="".join(lines), capture_output=True, text=True)
+    out = []
+    for b, f in [(b, 8 - b) for b in (2, 3, 4, 5, 6, 7)] + [(2, 0), (3, 0), (4, 0)]:
+        codes = list(range(-128, 128)) if f else list(range(-8, 8))
+        pick = lambda: [int(c) for c in rng.choice(codes, 4)]
+        for tz in (0.0, 1e-20, 3e-5, 0.01, 0.2):
+            for code in codes:  # every code, in every byte, below and above its decision points
+                for pos in range(4):
+                    c, d = pick(), [float(x) for x in rng.normal(0, 0.1, 4)]
+                    c[pos] = code
+                    v = Fraction(code, 2 ** f)
+                    point = math.floor(v) + Fraction(1, 2) + int(rng.integers(-1, 2))
+                    d[pos] = float(point - v) + float(rng.choice([0.0, 1e-21, -1e-21, 1e-6, -1e-6, tz, -tz, 1.1 * tz, -1.1 * tz, 0.1]))
+                    out.append((f, b, tz, c, d))
+        for scale in (1e-30, 1e-5, 0.1, 0.4, 3.0, 60.0, 3e4, 1e6):
+            for _ in range(200):
+                tz = float(rng.choice([0.0, 1e-5, 1e-3])) * scale
+                out.append((f, b, tz, pick(), [float(x) for x in rng.normal(0, scale, 4)]))
+    return [(f, b, float(np.float32(tz)), c, [float(np.float32(x)) for x in d]) for f, b, tz, c, d in out]
+
+
+def test_certain_decisions_hold_for_every_delta_within_the_bound(decide_driver):
+    """What the grid pass decides from a float32 delta, on the byte-parallel path (where its regime holds and nothing
+    clips) and on the rounding path, is round-half-even(code 2^-f + delta) for every delta within the error bound,
+    unless it is marked for settling in float64; the clip marks are those of results past the grid."""
+    cases = _decisions()
+    lines = "".join(f"{f} {b} {_bits(tz):x} " + " ".join(f"{_bits(x):x} {c}" for x, c in zip(d, code)) + "\n"
+                    for f, b, tz, code, d in cases)
+    r = subprocess.run([decide_driver], input=lines, capture_output=True, text=True)
     assert r.returncode == 0
-    out = [tuple(int(t, 16) for t in line.split()) for line in r.stdout.splitlines()]
-    assert len(out) == len(cases)
+    rows = [line.split() for line in r.stdout.splitlines()]
+    assert len(rows) == len(cases)
+    sure = {"bytes": [0, 0], "rounding": [0, 0]}
     bad = []
-    for (codes, incs, f, b), (q, clip) in zip(cases, out):
+    for (f, b, tz, codes, deltas), row in zip(cases, rows):
         lo, hi = -(1 << (b - 1)), (1 << (b - 1)) - 1
-        eps = Fraction(1, 2 ** (f + 3))  # |delta| below 2^-f: only ties depend on its sign
+        regime, q, clip, sure1 = int(row[0]), int(row[1], 16), int(row[2], 16), int(row[3], 16)
+        v2, sure2 = [int(x) for x in row[4:8]], int(row[8], 16)
         for j in range(4):
-            code = int(codes[j]) - 256 if codes[j] >= 128 else int(codes[j])
-            u = Fraction(code, 2 ** f) + (eps if incs[j] else -eps)
-            want = _rne(u)
-            clipped = want > hi or want < lo
-            got_clip = (clip >> (8 * j + 7)) & 1
-            if got_clip != int(clipped):
-                bad.append(("clip", code, f, int(incs[j]), want, got_clip))
-            elif not clipped and ((q >> (8 * j)) & 0xFF) != (want & (0xFF if b > 4 else 15)):
-                bad.append(("q", code, f, int(incs[j]), want, (q >> (8 * j)) & 0xFF))
+            u = Fraction(codes[j], 2 ** f) + Fraction(deltas[j])
+            ends = {_rne(u - Fraction(tz)), _rne(u + Fraction(tz))}
+            if regime:
+                ok = sure1 >> j & 1
+                sure["bytes"][ok] += 1
+                got = q >> (8 * j) & (0xFF if b > 4 else 15)
+                if ok and (clip >> (8 * j + 7) & 1) != int(max(ends) > hi):
+                    bad.append(("clip", f, b, tz, codes[j], deltas[j], ends))
+                elif ok and max(ends) <= hi and {e & (0xFF if b > 4 else 15) for e in ends} != {got}:
+                    bad.append(("bytes", f, b, tz, codes[j], deltas[j], ends, got))
+            ok = sure2 >> j & 1
+            sure["rounding"][ok] += 1
+            if ok and ends != {v2[j]}:
+                bad.append(("rounding", f, b, tz, codes[j], deltas[j], ends, v2[j]))
     assert not bad, bad[:10]
+    # both answers occur, and a bound that marked everything would pass for nothing
+    assert all(min(n) > 1000 and n[1] > n[0] for n in sure.values()), sure
+
+
+def test_an_exactly_zero_delta_rounds_phi0_half_to_even(decide_driver):
+    """delta = 0 (B at its initialisation) is decided by the rounding path alone, ties and all."""
+    cases = [(8 - b if fmt else 0, b, c) for b in range(2, 8) for fmt in ((1, 0) if b <= 4 else (1,))
+             for c in (range(-128, 128) if fmt else range(-8, 8))]
+    lines = "".join(f"{f} {b} 0 " + " ".join(f"0 {c}" for _ in range(4)) + "\n" for f, b, c in cases)
+    r = subprocess.run([decide_driver], input=lines, capture_output=True, text=True)
+    got = [[int(x) for x in line.split()[4:8]] for line in r.stdout.splitlines()]
+    assert len(got) == len(cases)
+    assert all(g == [_rne(Fraction(c, 2 ** f))] * 4 for (f, b, c), g in zip(cases, got))
