@@ -1,8 +1,6 @@
 // Dispatch of the bf16 MFMA GEMM variants (one translation unit per variant
 // family, see gemm_impl.h) and the deterministic reduction of the rank-r
 // partial products.
-#include <algorithm>
-
 #include "kernels.h"
 
 namespace lrqat {
@@ -90,58 +88,6 @@ hipError_t launch_reduce2(const Reduce2Args& ra0, hipStream_t st) {
   }
   k_reduce2<<<unsigned(ra.nblocks + nds), 256, 0, st>>>(ra);
   return hipGetLastError();
-}
-
-// Tiles: the time of a launch is its rounds over the chip (256 CUs; two 128 x 128 blocks share one) times
-// the time of a round, and a 256 x 256 tile has the best rate but leaves CUs idle when an output has few
-// of them.  The weights below are rounds of each tile against a round of 256 x 256 tiles, measured on
-// outputs that fill the chip (4096 x 4096, T = 8192: forward 226 us with 256 x 256 tiles, 251 / 286 / 279 with
-// 256 x 128, 128 x 256, 128 x 128; dX 246, 289 / 312 / 347) or at most once.  What the choice gives: forward of
-// 640 tokens through 11008 x 4096 (129 tiles of 256 x 256) 98 -> 70 us, of 4096 tokens through 1024 x 4096 94 ->
-// 49; dX of 2048 tokens through 14336 x 4096 (128 tiles) 339 -> 254.
-//
-// dW: its epilogue and its partial sums grow with the number of tiles, so an output of more than 128 tiles of
-// 256 x 256 keeps them.  A smaller one, which would leave half the chip without a tile, takes 128 x 128 tiles if one
-// per CU covers it, else 256 x 128 (T = 4096: 1024 x 4096, 256 small tiles, 146 -> 70 us; 2048 x 2500, 153 -> 96 in
-// 256 x 128, 105 in 128 x 128).  Where even 128 x 128 tiles are at most half the CUs, the blocks of a tile share its
-// tokens, and a second launch adds their float32 sums before anything is rounded: at least eight K-tiles for
-// each, which is what that launch costs (1024 x 1024: T = 2048 42 -> 30 us in four ranges, T = 512 21 -> 23 in
-// two), and 16 ranges at most, which one block adds in turn (256 x 256, T = 8192: 124 us, 36 in 16, 42 in 32).
-GemmPlan gemm_plan(GemmVariant v, bool act, bool grouped, bool al16, int64_t M, int64_t N, int64_t K) {
-  GemmPlan g;
-  auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-  if (v == kDw) {
-    const int64_t n22 = tiles(128, 128);
-    if (n22 <= 256) {
-      g.tm = g.tn = 128;
-      g.split = int(std::max<int64_t>(1, std::min<int64_t>({256 / n22, (K + 63) / 64 / 8, 16})));
-    } else if (tiles(256, 256) <= 128) {
-      g.tn = 128;
-    }
-    return g;
-  }
-  if (!al16) {  // rows off 16 bytes: the small tile, whose second block per CU hides the loads that cross lines
-    g.tm = g.tn = 128;
-    return g;
-  }
-  struct Cost { double t42, t24, t22, t22_one; };  // a round of 256 x 128, 128 x 256, 128 x 128 (two and one per CU)
-  constexpr double never = 1e30;  // the other tiles are ahead wherever it could be taken
-  const Cost c = v == kFwd ? (act ? Cost{never, never, 0.54, 0.46} : Cost{0.57, never, 0.63, 0.44})
-                           : (grouped ? Cost{0.78, 0.74, 0.88, 0.55} : Cost{0.59, 0.63, 0.70, 0.45});
-  auto rounds = [](int64_t n, int64_t slots) { return double((n + slots - 1) / slots); };
-  double best = rounds(tiles(256, 256), 256);
-  auto offer = [&](int tm, int tn, double cost) {
-    if (cost < best) {
-      best = cost;
-      g.tm = tm;
-      g.tn = tn;
-    }
-  };
-  offer(256, 128, rounds(tiles(256, 128), 256) * c.t42);
-  offer(128, 256, rounds(tiles(128, 256), 256) * c.t24);
-  const int64_t n22 = tiles(128, 128);
-  offer(128, 128, n22 <= 256 ? c.t22_one : rounds(n22, 512) * c.t22);
-  return g;
 }
 
 hipError_t launch_gemm(GemmVariant v, bool act, bool grouped, int opt, const GemmArgs& p, hipStream_t st) {

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.h"
+#include "gemm_plan.h"
 
 namespace lrqat {
 
@@ -25,17 +26,6 @@ struct GridArgs {
   int64_t ldm;           // 16-bit words per row of mout (kq / 16)
   float tau_coef;        // set by launch_grid: error-bound coefficient of the float32 delta
   int nit;               // set by launch_grid: 16-row rounds per wave
-};
-
-// bf16 MFMA GEMM family.  C[M][N] = sum_K a(M, K) b(K, N) with the operand
-// sources and epilogue chosen by the kernel variant.
-enum GemmVariant { kFwd = 0, kDx = 1, kDw = 2 };
-
-// Work split of a GEMM: block tiles of tm x tn outputs (256 or 128 each); for dW in 128 x 128 tiles `split`
-// blocks per tile, each for a range of the tokens.
-struct GemmPlan {
-  int tm = 256, tn = 256;
-  int split = 1;
 };
 
 struct GemmArgs {
@@ -80,16 +70,6 @@ enum : int {
 
 constexpr int kColPad = 256;  // q, mask and code rows are padded to a multiple of this
 
-// int8 tokens run on the int8 MFMA with one scale per output channel, and where int32 sums of products
-// up to 2^14 (16 q n) cannot wrap
-inline bool fwd_int8(bool act, bool grouped, int64_t K) { return act && !grouped && K <= (int64_t(1) << 16); }
-// plan of a GEMM from its sizes; al16: its bfloat16 rows start on 16 bytes (and a K-contiguous one has no
-// partial K-tile)
-GemmPlan gemm_plan(GemmVariant v, bool act, bool grouped, bool al16, int64_t M, int64_t N, int64_t K);
-inline bool gemm_al16(GemmVariant v, bool act, int64_t K, int64_t lda, int64_t ldb) {
-  if (v == kDw) return lda % 8 == 0 && ldb % 8 == 0;
-  return act || (lda % 8 == 0 && K % 64 == 0);
-}
 hipError_t launch_minmax_scale(const float* W0, int64_t m, int64_t k, int64_t gsize, int bits, float* s0, int32_t* z0,
                                hipStream_t st);
 hipError_t launch_encode(const float* W0, const float* s0, const int32_t* z0, int64_t m, int64_t k, int64_t gsize,
@@ -111,12 +91,6 @@ hipError_t launch_dx_i4(bool grouped, bool zp, const GemmArgs& p, hipStream_t st
 hipError_t launch_dx_i8(bool grouped, bool zp, const GemmArgs& p, hipStream_t st);       // gemm_dx_q8.hip
 hipError_t launch_dw_pc(const GemmArgs& p, hipStream_t st);                              // gemm_dw.hip
 hipError_t launch_dw_grp(const GemmArgs& p, hipStream_t st);                             // gemm_dw_grp.hip
-// Few tokens: the weights streamed (gemm_small.hip) against the tiles of the general GEMM.  Up to 64 tokens
-// the streaming kernel reads them once and is ahead on every layer measured (14336 x 4096, T = 64: 39
-// against 45 us); past that each 64 tokens read them again, which pays while its blocks (32 rows by 64
-// tokens) are few: 1024 x 4096, T = 512 (256 blocks) 26 against 45 us, 4096 x 4096, T = 192 (384) 37 against 37,
-// T = 256 (512) 44 against 37, 14336 x 4096, T = 96 (896) 59 against 45.
-inline bool fwd_small(int64_t T, int64_t m) { return T <= 64 || (T <= 512 && ((m + 31) / 32) * ((T + 63) / 64) < 384); }
 hipError_t launch_fwd_small(bool act, bool grouped, bool q8, const GemmArgs& p, hipStream_t st);
 // rows of w bytes re-laid with a leading dimension of ldd bytes, zero-filled
 hipError_t launch_repack_rows(const uint8_t* src, int64_t m, int64_t w, uint8_t* dst, int64_t ldd, hipStream_t st);

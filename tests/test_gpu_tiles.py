@@ -29,11 +29,11 @@ CASES = [
     (130, 258, 514, 5, 4, "int_packed2", 0, 0, True),    # rows on dwords, a partial K-tile, zero offset
     (131, 320, 520, 32, 6, "q8", 0, 0, False),           # m odd (dX, dW rows), k a whole number of K-tiles
     (192, 323, 576, 16, 3, "q8", 0, 0, False),           # k odd, m aligned
-    (256, 1030, 1300, 20, 4, "int_packed2", 0, 0, False),  # dW split over the tokens, unaligned rows
-    (264, 512, 2050, 33, 4, "q8", 128, 0, True),         # dW split with a short last part, groups with offsets
-    (256, 4096, 2048, 4, 4, "int_packed2", 0, 0, False),  # dX in 256 x 128 tiles
-    (128, 11008, 640, 4, 4, "int_packed2", 0, 0, False),  # dX in 128 x 256 tiles
-    (4096, 128, 2048, 4, 4, "q8", 0, 0, False),          # forward in 256 x 128 tiles
+    (256, 1030, 1300, 20, 4, "int_packed2", 0, 0, False),  # dW in ranges of the tokens, unaligned rows
+    (264, 512, 2050, 33, 4, "q8", 128, 0, True),         # dW in ranges of the tokens, groups with offsets
+    (256, 4096, 2048, 4, 4, "int_packed2", 0, 0, False),
+    (128, 11008, 640, 4, 4, "int_packed2", 0, 0, False),
+    (4096, 128, 2048, 4, 4, "q8", 0, 0, False),
     (320, 640, 530, 8, 4, "int_packed2", 0, 8, True),    # int8 forward with a zero offset
     (257, 384, 600, 8, 6, "q8", 0, 8, True),             # int8 forward on an int8 grid
     (136, 1000, 520, 8, 4, "int_packed2", 0, 8, False),  # int8 forward, k no multiple of its 128-value K-tile
@@ -85,12 +85,62 @@ def test_bytes_past_a_tensor_stay_out(lr, m, k, T):
     check_layer(lr, c)
 
 
+# Outputs large enough for the larger tiles, with each form of the weight operand.
+LARGE = [
+    (4096, 192, 2304, 4, 4, "q8", 0, 0, True),
+    (4096, 192, 2304, 4, 6, "q8", 0, 0, False),
+    (4096, 192, 2304, 4, 7, "q8", 0, 0, True),
+    (4096, 256, 2304, 4, 3, "q8", 128, 0, True),
+    (4096, 256, 2304, 4, 6, "q8", 128, 0, False),
+    (4096, 200, 2304, 4, 4, "int_packed2", 0, 8, False),
+    (4096, 200, 2304, 4, 4, "q8", 0, 8, True),
+    (4096, 200, 2304, 4, 6, "q8", 0, 8, True),
+    (4096, 256, 2304, 4, 4, "int_packed2", 64, 8, True),
+    (4096, 128, 2048, 4, 6, "q8", 0, 0, True),
+    (4096, 128, 2048, 4, 4, "q8", 64, 0, True),
+    (192, 4096, 2304, 4, 4, "q8", 0, 0, True),
+    (192, 4096, 2304, 4, 6, "q8", 0, 0, False),
+    (192, 4096, 2304, 4, 6, "q8", 128, 0, True),
+    (256, 4096, 2048, 4, 6, "q8", 0, 0, True),
+    (256, 4096, 2048, 4, 4, "q8", 128, 0, True),
+    (128, 11008, 640, 4, 6, "q8", 0, 0, True),
+    (128, 10880, 768, 4, 6, "q8", 128, 0, True),
+]
+
+# The tiles (and token ranges) that the host chooses for cases of these lists: (GEMM, m, k, T, group, act).
+REACHED = {
+    (256, 256, 1): [("fwd", 4096, 192, 2304, 0, 0), ("fwd", 4096, 256, 2304, 128, 0), ("fwd", 4096, 200, 2304, 0, 8),
+                    ("fwd", 4096, 256, 2304, 64, 8), ("dx", 192, 4096, 2304, 0, 0), ("dx", 192, 4096, 2304, 128, 0),
+                    ("dw", 2901, 2903, 66, 0, 0), ("dw", 2902, 2906, 66, 0, 0), ("dw", 2901, 2944, 66, 128, 0)],
+    (256, 128, 1): [("fwd", 4096, 128, 2048, 0, 0), ("fwd", 4096, 128, 2048, 64, 0), ("dx", 256, 4096, 2048, 0, 0),
+                    ("dx", 128, 10880, 768, 128, 0), ("dw", 2050, 2100, 70, 0, 0), ("dw", 2051, 2101, 130, 0, 0),
+                    ("dw", 2056, 2176, 64, 128, 0)],
+    (128, 256, 1): [("dx", 128, 11008, 640, 0, 0), ("dx", 256, 4096, 2048, 128, 0)],
+    (128, 128, 1): [("fwd", 136, 640, 520, 64, 8), ("fwd", 257, 384, 600, 0, 8), ("fwd", 129, 255, 513, 0, 0),
+                    ("dx", 129, 255, 513, 0, 0), ("dw", 129, 255, 513, 0, 0), ("dx", 264, 512, 2050, 128, 0)],
+    (128, 128, 2): [("dw", 129, 257, 1030, 0, 0)],
+    (128, 128, 4): [("dw", 384, 640, 2050, 128, 0)],
+    (128, 128, 16): [("dw", 130, 130, 8192, 0, 0)],
+}
+
+
+@pytest.mark.parametrize("case", LARGE, ids=[f"m{s[0]}k{s[1]}T{s[2]}b{s[4]}g{s[6]}a{s[7]}{'z' if s[8] else ''}" for s in LARGE])
+def test_large_tiles(lr, case):
+    m, k, T, r, bits, fmt, g, act, asym = case
+    c = Layer(lr, m, k, T, r, float(r), bits, fmt, g, act, "bf16", asym=asym, seed=800 + k + bits, b_std=0.02,
+              shift=0.01 if asym else 0.0)
+    check_layer(lr, c)
+
+
 DW = [
     # m, k, T, r, bits, fmt, g, asym
-    (2050, 2100, 70, 5, 4, "int_packed2", 0, False),     # 256 x 128 tiles, rows on dwords, one past the tiles in both
-    (2051, 2101, 130, 33, 4, "q8", 0, False),            # the same with odd rows, ranks past one block of 32
-    (2056, 2176, 64, 8, 3, "int_packed2", 128, True),    # the same with groups and offsets, 16-byte rows
-    (129, 257, 1030, 32, 6, "q8", 0, False),             # 128 x 128, two ranges of tokens (8 and 9 K-tiles), odd rows
+    (2050, 2100, 70, 5, 4, "int_packed2", 0, False),     # rows on dwords, past the 256 x 128 tiles in both directions
+    (2051, 2101, 130, 33, 4, "q8", 0, False),            # odd rows, ranks past one block of 32
+    (2056, 2176, 64, 8, 3, "int_packed2", 128, True),    # groups and offsets, 16-byte rows
+    (2901, 2903, 66, 8, 4, "q8", 0, False),              # 256 x 256 tiles with odd rows
+    (2902, 2906, 66, 4, 4, "int_packed2", 0, True),      # and rows on dwords, offsets
+    (2901, 2944, 66, 4, 4, "q8", 128, False),            # and groups
+    (129, 257, 1030, 32, 6, "q8", 0, False),             # two ranges of tokens (8 and 9 K-tiles), odd rows
     (384, 640, 2050, 20, 4, "int_packed2", 128, False),  # four ranges, a last K-tile of two tokens, groups
     (130, 130, 8192, 8, 4, "q8", 0, True),               # 16 ranges, offsets, rows on dwords
 ]

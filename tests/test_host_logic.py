@@ -153,3 +153,28 @@ def test_an_exactly_zero_delta_rounds_phi0_half_to_even(decide_driver):
     got = [[int(x) for x in line.split()[4:8]] for line in r.stdout.splitlines()]
     assert len(got) == len(cases)
     assert all(g == [_rne(Fraction(c, 2 ** f))] * 4 for (f, b, c), g in zip(cases, got))
+
+
+def test_tile_cases_reach_their_tiles(tmp_path):
+    """The GPU tests of the GEMM tiles run the tiles that they are meant to run."""
+    tiles = pytest.importorskip("test_gpu_tiles")
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("g++ not available")
+    exe = str(tmp_path / "gemm_plan_host")
+    cmd = [gxx, "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2406_06385_amd", "csrc"),
+           os.path.join(ROOT, "tests", "host", "gemm_plan_host.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    run = {c[:3] + c[6:8] for c in tiles.CASES + tiles.LARGE} | {c[:3] + (c[6], 0) for c in tiles.DW}
+    lines, want = [], []
+    for (tm, tn, split), claims in tiles.REACHED.items():
+        for gemm, m, k, T, group, act in claims:
+            assert (m, k, T, group, act) in run
+            kpad = -(-k // 256) * 256
+            v, size, ld = {"fwd": (0, (T, m, k), (kpad if act else k, kpad // 2)), "dx": (1, (T, k, m), (m, kpad // 2)),
+                           "dw": (2, (m, k, T), (m, kpad if act else k))}[gemm]
+            lines.append(" ".join(str(x) for x in (v, int(bool(act) and v == 0), int(bool(group)), *size, *ld)))
+            want.append(f"0 {tm} {tn} {split}")
+    r = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True)
+    assert [(a, b) for a, b in zip(lines, r.stdout.splitlines())] == list(zip(lines, want))
