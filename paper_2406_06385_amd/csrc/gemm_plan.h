@@ -29,10 +29,12 @@ inline bool gemm_al16(GemmVariant v, bool act, int64_t K, int64_t lda, int64_t l
 }
 
 // Few tokens: the weights streamed (gemm_small.hip) against the tiles of the general GEMM.  Up to 64 tokens
-// the streaming kernel reads them once and is ahead on every layer measured (14336 x 4096, T = 64: 39
-// against 45 us); past that each 64 tokens read them again, which pays while its blocks (32 rows by 64
-// tokens) are few: 1024 x 4096, T = 512 (256 blocks) 26 against 45 us, 4096 x 4096, T = 192 (384) 37 against 37,
-// T = 256 (512) 44 against 37, 14336 x 4096, T = 96 (896) 59 against 45.
+// the streaming kernel reads them once; past that each 64 tokens read them again, which pays while its
+// blocks (32 rows by 64 tokens) are few.  Streamed / tiled, in us: 4096 x 4096, T = 128 (256 blocks) 28 / 33, with groups
+// of 128 29 / 46, int8 14 / 24, int8 with groups 20 / 55; T = 256 (512) 46 / 33, 50 / 46, 24 / 24, 33 / 55.  The length
+// of K changes both alike (1024 x 14336, T = 512, 256 blocks: 83 / 138; 1024 x 1024: 11 / 13).  The widest layers
+// come out even near 64 tokens: 14336 x 4096, T = 48 36 / 38, T = 64 43 / 38, with groups 45 / 47, int8 23 / 22, rows off 16
+// bytes 47 / 94.
 inline bool fwd_small(int64_t T, int64_t m) { return T <= 64 || (T <= 512 && ((m + 31) / 32) * ((T + 63) / 64) < 384); }
 
 // Tiles: the time of a launch is its rounds over the chip (256 CUs; two 128 x 128 blocks share one) times

@@ -238,12 +238,13 @@ hipError_t launch_rg(const GemmArgs& p, hipStream_t st) {
 
 // Token groups of 16 per block by the token count, four at most (eight held too many registers: 128
 // tokens through 4096 x 4096 took 51 us, 26 as two blocks of four).  A second row group halves the
-// token loads per weight: with four token groups, and with two where the rows still give 512 blocks
-// (14336 x 4096, T = 32 38 -> 25 us; 1024 x 4096 would lose blocks, 11.1 -> 12.1).
+// token loads per weight: with four token groups, and with two where groups of 16 rows are more blocks than
+// CUs (K = 4096, T = 32, one -> two row groups: m = 4096 16 -> 14 us, and group-wise 17 -> 16, int8 9 -> 10, int8
+// group-wise 13 -> 14; 6144 21 -> 14, 24 -> 17, 14 -> 10, 17 -> 14; 14336 36 -> 25; 1024 13 -> 14).
 template <int MODE, bool GRP, bool Q8>
 hipError_t launch_mode(const GemmArgs& p, hipStream_t st) {
   if (p.M <= 16) return launch_rg<MODE, GRP, Q8, 1, 1>(p, st);
-  if (p.M <= 32) return p.N >= 8192 ? launch_rg<MODE, GRP, Q8, 2, 2>(p, st) : launch_rg<MODE, GRP, Q8, 2, 1>(p, st);
+  if (p.M <= 32) return p.N > 4096 ? launch_rg<MODE, GRP, Q8, 2, 2>(p, st) : launch_rg<MODE, GRP, Q8, 2, 1>(p, st);
   return launch_rg<MODE, GRP, Q8, 4, 2>(p, st);
 }
 
