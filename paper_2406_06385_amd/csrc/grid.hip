@@ -295,16 +295,28 @@ __device__ __forceinline__ void grid_clear(const GridArgs& a, GridOut& o, int64_
   }
 }
 
+// q = Phi0 on a 4-bit grid.
+__device__ __forceinline__ void grid_copy(const GridArgs& a, const PhiRegs& P, int64_t c16, bool edge, GridOut& o) {
+  o.w0 = P.w[0];
+  o.w1 = P.w[1];
+  o.mb = 0xFFFFu;
+  if (edge) grid_clear(a, o, c16, false);
+}
+
 // Rounding decision, clip, packing and mask of one 16 x 64 wave tile (INT-b Phi0 whose |delta| bound is
 // below 1/2 on the whole tile has been copied already).  Returns whether one of
 // the lane's elements lies within the error bound tau of a rounding point: its result is tentative, and the
 // lane's piece is to be queued for grid_drain.
+//  * COPY (r > 32), INT4 on a 4-bit grid, |delta| < 1/2: Phi0 itself.  The norm bound grows with r and misses
+//    most of these tiles (4096 x 4096, r = 64, delta of 0.05: 22.0 -> 19.0 us; 14336 x 4096 60.7 -> 51.0), which it
+//    rarely does at r <= 32, where the maximum costs more than it saves (14336 x 4096, r = 32, delta of 0.05 23.6 ->
+//    23.2, of 0.2 43.3 -> 45.7);
 //  * Q8, |delta| < 1/2: n + [w > 0] (grid_w), formed byte-parallel;
 //  * else u = Phi0 + delta is rounded in float32 by adding kGridMagic: the nearest integer v is then the low
 //    byte of the sum's bits.  Where delta is identically zero (tau < 0: a zero A row;
 //    zero_delta: zero B columns, the adapters' initial state) this is round-half-even of Phi0 itself.
 // edge (uniform): the tile has columns past k.
-template <bool PACKED, bool MASK, bool B4, bool Q8OUT>
+template <bool PACKED, bool MASK, bool B4, bool Q8OUT, bool COPY>
 __device__ __forceinline__ bool grid_decide(const GridArgs& a, const PhiRegs& P, const f32x4 (&acc)[4], float tau, bool zero_delta,
                                                 int64_t row, int64_t c16, bool edge, GridOut& o) {
   const int bits = B4 ? 4 : a.bits;  // B4: the common 4-bit grid, constant for the compiler
@@ -326,13 +338,23 @@ __device__ __forceinline__ bool grid_decide(const GridArgs& a, const PhiRegs& P,
     }
   };
   bool done = false;
-  if constexpr (!PACKED) {
+  // every |delta| of the wave's tile below 1/2, its error bound included (a NaN makes tau infinite)
+  bool below = false;
+  if (!PACKED || (COPY && bits == 4)) {
     float amx = 0.f;
 #pragma unroll
     for (int g = 0; g < 4; ++g)
 #pragma unroll
       for (int v = 0; v < 4; ++v) amx = fmaxf(amx, fabsf(acc[g][v]));
-    if (!zero_delta && !__builtin_amdgcn_ballot_w64(!(amx * fabsf(a.c) < 0.5f - tz - 0x1p-20f && tau >= 0.f))) {
+    below = !zero_delta && !__builtin_amdgcn_ballot_w64(!(amx * fabsf(a.c) < 0.5f - tz - 0x1p-20f && tau >= 0.f));
+  }
+  if constexpr (PACKED) {
+    if (below) {
+      grid_copy(a, P, c16, edge, o);
+      return false;
+    }
+  } else {
+    if (below) {
       auto w_of = [&](int g, int v) { return grid_w(P.w[g], v, f, acc[g][v], a.c); };
       float wmn = __builtin_inff();
       uint32_t clip = 0;
@@ -500,14 +522,6 @@ __device__ __forceinline__ void grid_store(const GridArgs& a, const GridOut& o, 
     }
     if constexpr (MASK) a.mout[row * a.ldm + (c16 >> 4)] = uint16_t(mb);
   }
-}
-
-// q = Phi0 on a 4-bit grid.
-__device__ __forceinline__ void grid_copy(const GridArgs& a, const PhiRegs& P, int64_t c16, bool edge, GridOut& o) {
-  o.w0 = P.w[0];
-  o.w1 = P.w[1];
-  o.mb = 0xFFFFu;
-  if (edge) grid_clear(a, o, c16, false);
 }
 
 // A lane's norm bound of a row or column; infinite where a NaN would be lost in a maximum.
@@ -731,7 +745,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
     const float na = norm_bound_nan(ass, amx, a.r);
     const float tau = na == 0.f ? -1.f : a.tau_coef * na * nb;
     GridOut o;
-    const bool need = grid_decide<PACKED, MASK, B4, Q8OUT>(a, Pc, acc, tau, nb == 0.f, row, c16, col0 + GR_COLS > a.k, o);
+    const bool need = grid_decide<PACKED, MASK, B4, Q8OUT, !ONEK>(a, Pc, acc, tau, nb == 0.f, row, c16, col0 + GR_COLS > a.k, o);
     if (need) queue[wave][atomicAdd(&nqueue[wave], 1)] = uint16_t((row - rb0 * 16) << 4 | ((c16 - (col0 - GR_COLS * wave)) >> 4));
     grid_store<MASK, Q8OUT>(a, o, row, c16);
   }
@@ -1178,7 +1192,7 @@ __global__ __launch_bounds__(GR_THREADS, MULTI || Q8OUT ? 2 : 3) void k_grid_w(G
         }
         // -1 where delta is exactly zero (a zero A row), so that no element is re-decided there
         const float tau = na == 0.f ? -1.f : a.tau_coef * na * nb;
-        const bool need = grid_decide<PACKED, MASK, B4, Q8OUT>(a, Pj, acc, tau, nb == 0.f, row, c16, edge, o);
+        const bool need = grid_decide<PACKED, MASK, B4, Q8OUT, MULTI>(a, Pj, acc, tau, nb == 0.f, row, c16, edge, o);
         if (need) queue[wave][atomicAdd(&nqueue[wave], 1)] = uint16_t((row - (rb0 - wave) * 16) << 4 | ((c16 - strip0) >> 4));
       }
 #pragma unroll

@@ -147,3 +147,24 @@ def test_wide_packed_copy_regime_rounds(lr, variant):
     else:
         assert moved > 1000, "the scaled rows should move codes"
     check_full(lr, c)
+
+
+@pytest.mark.parametrize("m,k,r", [(M, K, 64), (70, 310, 40)], ids=["wide", "per_wave"])
+@pytest.mark.parametrize("rows", ["all", "some"])
+def test_packed_copy_by_the_product(lr, m, k, r, rows):
+    """Packed INT4 Phi0 with r > 32 whose |delta| stays below 1/2 while the norm bound does not: q = Phi0, copied
+    by the product itself ('all'); with the rows of every third 16-row block scaled up, those are decided element by
+    element beside it ('some')."""
+    _log(f"[packed copy by the product {m}x{k} r{r} {rows}]")
+    c = Case(lr, m, k, 64, r, float(r), 4, "int_packed2", 0, 0, "bf16", seed=97,
+             b_std=0.07 / math.sqrt(r / (3.0 * k)))  # delta of 0.07, |delta| < 0.45 over 8.7 M elements
+    bound = np.linalg.norm(c.A.astype(np.float64), axis=1).min() * np.linalg.norm(c.B.astype(np.float64), axis=0).max()
+    assert bound > 0.5
+    if rows == "some":
+        c.A[(np.arange(m) // 16) % 3 == 1] *= np.float32(4.0)
+        c.d_A = torch.from_numpy(c.A).cuda()
+    check_setup(c)
+    q_ref, near = check_merge(lr, c, allow_near=rows == "some")
+    moved = int((q_ref != O.decode_phi0(c.phi0_ref, 4, "int_packed2")).sum())
+    assert moved == 0 if rows == "all" else moved > 0
+    check_full(lr, c)
