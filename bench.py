@@ -219,9 +219,9 @@ def kernel_flops(name, wl):
 # Sources each library kernel is compiled from: a traffic record stays valid
 # while these files are unchanged.
 KERNEL_SOURCES = {
-    "gemm_fwd": ["gemm_impl.h", "gemm_fwd.hip", "kernels.h", "common.h"],
-    "gemm_dx": ["gemm_impl.h", "gemm_dx.hip", "kernels.h", "common.h"],
-    "gemm_dw": ["gemm_impl.h", "gemm_dw.hip", "kernels.h", "common.h"],
+    "gemm_fwd": ["gemm_impl.h", "gemm_plan.h", "gemm_fwd.hip", "kernels.h", "common.h"],
+    "gemm_dx": ["gemm_impl.h", "gemm_plan.h", "gemm_dx.hip", "kernels.h", "common.h"],
+    "gemm_dw": ["gemm_impl.h", "gemm_plan.h", "gemm_dw.hip", "kernels.h", "common.h"],
     "grid": ["grid.hip", "grid_swar.h", "kernels.h", "common.h"],
     "reduce": ["gemm.hip", "kernels.h", "common.h"],
 }

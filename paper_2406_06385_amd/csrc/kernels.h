@@ -32,7 +32,7 @@ struct GemmArgs {
   int64_t M, N, K;
   const void* a;          // kFwd: X bf16 [T][k] or n int8 [T][lda]; kDx: dY [T][m]; kDw: dY [T][m]
   int64_t lda;
-  const void* b;          // kFwd/kDx: q [m][ldb], packed int4 or int8; kDw: X bf16 [T][k] or n int8 [T][ldb]
+  const void* b;          // kFwd/kDx: q [m][ldb], packed int4 or int8; kDw: X (W4A8: X_hat) bf16 [T][ldb]
   int64_t ldb;
   const float* s;         // weight scale [m] or [m][ngroups]
   const int32_t* z;       // zero offset, shaped like s (variants with kOptZ)
@@ -48,11 +48,11 @@ struct GemmArgs {
   int r;
   float* dA_part;         // kDw: [column tiles][M][r]
   float* dB_part;         // kDw: [row tiles][r][N]
-  const uint8_t* qd;      // kDw with kOptDs: q [M][ldqd] (packed int4, or int8 with kOptQ8)
+  const uint8_t* qd;      // kDw with ds_part: q [M][ldqd] (packed int4, or int8 with qd8)
   int64_t ldqd;
   float* ds_part;         // kDw, nullable: [M][ldds], sums over 32-column chunks of dW (q - z)
   int64_t ldds;
-  int qd8;                // kDw with ds_part: qd is int8
+  int qd8;
   float* tile_part;       // kDw with plan.split > 1: [split][tiles][tm * tn] sums of the token ranges
   GemmPlan plan;
 };
