@@ -576,6 +576,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
       for (int j = 0; j < 4; ++j) v[t][j] = col0 + cl + j < a.k ? v[t][j] : 0u;
       *reinterpret_cast<u32x4*>(raw + (4 * t + (lane >> 4)) * 64 + cl) = v[t];
     }
+    wave_sync();
     float y[4][8];
     float ss[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -586,6 +587,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
         ss[cb] = __builtin_fmaf(y[cb][e], y[cb][e], ss[cb]);
         bmx = fmaxf(bmx, fabsf(y[cb][e]));
       }
+    wave_sync();  // the raw rows are read: the fragments take their place
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
       u32x4 h, l;
@@ -661,6 +663,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
         // through the wave's LDS rows: lane l takes row l % 16, ranks 8 (l / 16) .. +7
 #pragma unroll
         for (int h = 0; h < 2; ++h) *reinterpret_cast<u32x4*>(&arow[wave][8 * h + (lane >> 3)][4 * (lane & 7)]) = xc[h];
+        wave_sync();
         const f32x4 u = *reinterpret_cast<const f32x4*>(&arow[wave][lane & 15][8 * (lane >> 4)]);
         const f32x4 w = *reinterpret_cast<const f32x4*>(&arow[wave][lane & 15][8 * (lane >> 4) + 4]);
 #pragma unroll
@@ -668,6 +671,7 @@ __global__ __launch_bounds__(GR_THREADS) void k_grid(GridArgs a) {
           x[e] = u[e];
           x[4 + e] = w[e];
         }
+        wave_sync();  // read before the next round's rows take their place
       } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = xa[e];
@@ -844,6 +848,7 @@ __global__ __launch_bounds__(GR_THREADS, MULTI || Q8OUT ? 2 : 3) void k_grid_w(G
   };
   auto stage_b_tail = [&]() {
     const float* raw = reinterpret_cast<const float*>(&bfrag[wave][0][0][0]);
+    wave_sync();
     float y[4][8];
     float ss[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -854,6 +859,7 @@ __global__ __launch_bounds__(GR_THREADS, MULTI || Q8OUT ? 2 : 3) void k_grid_w(G
         ss[cb] = __builtin_fmaf(y[cb][e], y[cb][e], ss[cb]);
         bmx = fmaxf(bmx, fabsf(y[cb][e]));
       }
+    wave_sync();  // the raw rows are read: the fragments take their place
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
       u32x4 h, l;
@@ -909,6 +915,7 @@ __global__ __launch_bounds__(GR_THREADS, MULTI || Q8OUT ? 2 : 3) void k_grid_w(G
   auto a_slice = [&](float (&xv)[8]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) *reinterpret_cast<u32x4*>(&arow[wave][8 * h + (lane >> 3)][4 * (lane & 7)]) = xc[h];
+    wave_sync();
     const f32x4 u = *reinterpret_cast<const f32x4*>(&arow[wave][lane & 15][8 * (lane >> 4)]);
     const f32x4 w = *reinterpret_cast<const f32x4*>(&arow[wave][lane & 15][8 * (lane >> 4) + 4]);
 #pragma unroll
@@ -916,6 +923,7 @@ __global__ __launch_bounds__(GR_THREADS, MULTI || Q8OUT ? 2 : 3) void k_grid_w(G
       xv[e] = u[e];
       xv[4 + e] = w[e];
     }
+    wave_sync();  // read before the next round's rows take their place
   };
 
   // q [row][cl0 .. cl0 + 63] (and the mask words) of one round, as the round loop below stores
